@@ -3,7 +3,7 @@
 // topology, and the optional pool after conv5).  Bandwidth-bound: every input element should cross
 // HBM once and every output once.
 //
-// Tiled kernel (LRN then pool, or pool only): a workgroup owns TPH x TPW pooled outputs and all C
+// Tiled kernel (LRN then pool): a workgroup owns TPH x TPW pooled outputs and all C
 // channels.  Phase 1 reads the (2 TPH + 1) x (2 TPW + 1) input pixels of its windows with 16-byte
 // channel vectors, computes the LRN of each input element once (the channel window is taken from
 // the neighbouring vectors, zero beyond the channel range, which equals clipping the window), and
@@ -18,7 +18,8 @@
 // so that each input element's LRN is computed about once rather than once per tile whose windows
 // reach it.
 //
-// The pool-then-LRN order uses a simple kernel with one thread per output element.
+// Plain pooling and the pool-then-LRN order pool straight from global memory, one thread per 16-byte
+// channel vector of an output pixel.
 #include <algorithm>
 #include <type_traits>
 
@@ -496,7 +497,86 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
   }
 }
 
-// Pool first, then LRN of the pooled vector: one thread per output element.
+// Pooling from global memory, for plain pooling and the pool-then-LRN order: one thread per 16-byte
+// channel vector of one output pixel.  It loads the (up to nine) input vectors of its clipped window at
+// once and takes their maxima in fp32; the LRN then needs at most four channels on either side, which
+// the threads of the neighbouring vectors hold: the pooled vectors (exact in the storage type) are
+// exchanged through LDS.  Bound by memory: an input vector lies in up to four windows, whose threads
+// are close by (a workgroup holds whole pixels, in row order, and the grid is in XCD order), so the
+// repeats are served by L1 and L2.  A tile of the input in LDS costs a barrier between two short phases
+// instead and leaves the loads of one phase alone in flight; one thread per output element with its
+// whole channel window repeats every load 2 HN + 1 times over.  64 maps of 55 x 55 x 96 in fp16, pool
+// then LRN: 10.4 us (4.4 TB/s of compulsory bytes; 103 us by element).  2000 maps of 13 x 13 x 256 in
+// bf16, pool alone: 28 us (7.5 TB/s with the input partly cached; 118 us through an LDS tile).
+// HN: half the LRN's channel window, or -1 for pooling alone.
+template <typename T, int HN>
+__global__ __launch_bounds__(256) void pool_vector_kernel(const T* __restrict__ in, T* __restrict__ out,
+                                                          KRuns runs, int C, float alpha_n, float beta,
+                                                          float k) {
+  constexpr int N = Vec<T>::N;
+  static_assert(HN <= N, "the channel window must fit one neighbouring vector");
+  typedef typename Vec<T>::type vec_t;
+  __shared__ vec_t s_pooled[HN > 0 ? 256 : 1];
+  const int G = C / N, PPB = 256 / G;  // threads per pixel, pixels per workgroup
+  const int nb = gridDim.x, xcd = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
+  int bid = xcd * per + min(xcd, rem) + blockIdx.x / 8;
+  const KRun& rn = runs.r[run_of(runs, bid)];
+  bid -= rn.first;
+  const int H = rn.H, W = rn.W, Ho = rn.Ho, Wo = rn.Wo;
+  const int plane = bid / rn.tiles_x;  // tiles_x workgroups of PPB pixels per plane
+  const int tid = threadIdx.x, p = tid / G, g = tid - p * G;
+  const int q = (bid - plane * rn.tiles_x) * PPB + p;
+  const bool live = p < PPB && q < Ho * Wo;
+  float m[N];
+  vec_t r;
+  if (live) {
+    const int oy = q / Wo, ox = q - oy * Wo;
+    const int h = min(3, H - 2 * oy), w = min(3, W - 2 * ox);  // the clipped window
+    const T* src = in + rn.in_off + plane * rn.in_stride + ((int64_t)2 * oy * W + 2 * ox) * C + g * N;
+    vec_t v[3][3];
+#pragma unroll
+    for (int y = 0; y < 3; ++y)
+#pragma unroll
+      for (int x = 0; x < 3; ++x)  // a tap past the edge repeats one inside
+        v[y][x] = *(const vec_t*)(src + ((int64_t)min(y, h - 1) * W + min(x, w - 1)) * C);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      m[i] = -INFINITY;
+#pragma unroll
+      for (int y = 0; y < 3; ++y)
+#pragma unroll
+        for (int x = 0; x < 3; ++x) m[i] = fmaxf(m[i], to_f32(v[y][x][i]));
+      r[i] = from_f32<T>(m[i]);
+    }
+  }
+  if constexpr (HN >= 0) {
+    float f[N + 2 * (HN > 0 ? HN : 0)];
+    if constexpr (HN > 0) {
+      s_pooled[tid] = r;
+      __syncthreads();
+    }
+    if (live) {
+      if constexpr (HN > 0) {
+        const vec_t lo = g > 0 ? s_pooled[tid - 1] : vec_t{}, hi = g + 1 < G ? s_pooled[tid + 1] : vec_t{};
+#pragma unroll
+        for (int i = 0; i < HN; ++i) f[i] = to_f32(lo[N - HN + i]), f[HN + N + i] = to_f32(hi[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < N; ++i) f[HN + i] = m[i];
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        float sq = 0.f;
+#pragma unroll
+        for (int j = 0; j <= 2 * HN; ++j) sq += f[i + j] * f[i + j];
+        r[i] = from_f32<T>(f[HN + i] * lrn_scale(sq, alpha_n, beta, k));
+      }
+    }
+  }
+  if (live) *(vec_t*)(out + rn.out_off + plane * rn.out_stride + (int64_t)q * C + g * N) = r;
+}
+
+// Pool first, then LRN of the pooled vector, for channel counts and pointers that do not divide into
+// 16-byte vectors: one thread per output element.
 template <typename T>
 __global__ __launch_bounds__(256) void pool_lrn_kernel(const T* __restrict__ in, T* __restrict__ out,
                                                        KRuns runs, int C, float alpha_n, float beta,
@@ -574,7 +654,33 @@ int run(const void* d_in, const MapRun* runs, int n_runs, int32_t C, bool lrn, b
       return (int64_t)q.tiles_x * q.tiles_y;
     });
   };
+  constexpr int N = Vec<T>::N;
+  // pool_vector_kernel over the runs of kr, one workgroup per 256 / (C / N) output pixels.
+  auto pool_vector = [&](auto hn_c) {
+    const int per = 256 / (C / N);
+    const int64_t blocks = fill_kruns(runs, n_runs, kr, [=](KRun& q) {
+      q.Ho = (q.H - 2) / 2 + 1, q.Wo = (q.W - 2) / 2 + 1;
+      q.tiles_x = (int)(((int64_t)q.Ho * q.Wo + per - 1) / per), q.tiles_y = 1;
+      return (int64_t)q.tiles_x;
+    });
+    if (blocks <= 0) return (int)hipErrorInvalidValue;
+    pool_vector_kernel<T, decltype(hn_c)::value><<<(unsigned)blocks, 256, 0, s>>>(in, out, kr, C, an, beta, k);
+    return (int)hipGetLastError();
+  };
   if (lrn && !lrn_first) {
+    // whole 16-byte vectors, at most 256 per pixel, from aligned pointers; a plane's vectors then
+    // start on 16 bytes too (its strides are whole pixels)
+    bool vec = C % N == 0 && C / N <= 256 && (((uintptr_t)in | (uintptr_t)out) & 15) == 0;
+    for (int i = 0; i < n_runs; ++i)
+      vec = vec && runs[i].in_off % N == 0 && runs[i].out_off % N == 0 && runs[i].in_stride % N == 0 &&
+            runs[i].out_stride % N == 0;
+    if (vec) switch (hn) {
+        case 0: return pool_vector(std::integral_constant<int, 0>{});
+        case 1: return pool_vector(std::integral_constant<int, 1>{});
+        case 2: return pool_vector(std::integral_constant<int, 2>{});
+        case 3: return pool_vector(std::integral_constant<int, 3>{});
+        case 4: return pool_vector(std::integral_constant<int, 4>{});
+      }
     const int64_t blocks = fill_kruns(runs, n_runs, kr, [=](KRun& q) {
       q.Ho = (q.H - 2) / 2 + 1, q.Wo = (q.W - 2) / 2 + 1;
       q.tiles_x = (int)(((int64_t)q.Ho * q.Wo * C + 255) / 256), q.tiles_y = 1;
@@ -584,7 +690,6 @@ int run(const void* d_in, const MapRun* runs, int n_runs, int32_t C, bool lrn, b
     pool_lrn_kernel<T><<<(unsigned)blocks, 256, 0, s>>>(in, out, kr, C, an, beta, k, hn);
     return (int)hipGetLastError();
   }
-  constexpr int N = Vec<T>::N;
   if (C % N || hn > 4) return (int)hipErrorInvalidValue;
   // Per-pixel kernel for the two channel counts of the network with the default window (n = 5).
   // Tiles: the largest whose input pixels fit one thread each (per part) and whose LDS tile stays
@@ -628,6 +733,7 @@ int run(const void* d_in, const MapRun* runs, int n_runs, int32_t C, bool lrn, b
   int TPH, TPW;
   pick_tile<T>(C, TPH, TPW);
   if (!TPH) return (int)hipErrorInvalidValue;
+  if (!lrn && C / N <= 256) return pool_vector(std::integral_constant<int, -1>{});
   const int64_t blocks = tiles(TPH, TPW);
   if (blocks <= 0) return (int)hipErrorInvalidValue;
   const size_t lds = (size_t)(2 * TPH + 1) * (2 * TPW + 1) * (C + N) * sizeof(T);

@@ -213,3 +213,38 @@ def test_conv1_ignores_row_padding(D, dt, W, pitch):
         assert_layer_close(chw(outs[0][i]), chw(outs[1][i]), dt, f"padded vs unpadded [{i}]")
         _, ref = oracle.net(x[i], w, pool5=True)
         assert_layer_close(chw(outs[0][i]), ref, dt, f"padded pool5 [{i}]")
+
+
+@pytest.mark.parametrize("dt", ["f32", "f16", "bf16"])
+# one vector per pixel; a vector count that does not divide 256; 256 vectors per pixel at 16 bits; a
+# channel count that is not whole vectors at 16 bits.  n = 3, 5, 9 channels; 2 x 2 is one clipped window.
+@pytest.mark.parametrize("C,shape,n", [(8, (3, 9, 7), 3), (96, (2, 2, 2), 5), (104, (1, 12, 15), 9),
+                                       (2048, (1, 3, 6), 5), (100, (1, 8, 5), 5), (256, (1, 5, 4), 1)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_pool_then_lrn_vectors(D, dt, C, shape, n, shift):
+    """Pool-then-LRN in vectors and (odd channel counts, unaligned pointers) by element, against fp64:
+    pooling is exact, so the result is off by its rounding and a few fp32 operations."""
+    N, H, W = shape
+    g = torch.Generator().manual_seed(C + H)
+    flat = (torch.randn(N * H * W * C + shift, generator=g) * 30).to("cuda", TORCH_DT[dt])
+    x = flat[shift:].view(N, H, W, C)
+    out = D.densenet_lrn_pool(x, DTS[dt], D.net_params(n=n, alpha=1e-3, lrn_before_pool=False)).double().cpu()
+    p = torch.nn.functional.max_pool2d(x.double().cpu().permute(0, 3, 1, 2), 3, 2, ceil_mode=True)
+    sq = torch.nn.functional.pad(p * p, (0, 0, 0, 0, n // 2, n // 2))
+    s = sum(sq[:, j:j + C] for j in range(n))
+    ref = (p * (1.0 + 1e-3 / n * s) ** -0.75).permute(0, 2, 3, 1)
+    half_ulp = {"f32": 2.0 ** -24, "f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dt]  # relative
+    # sums of n squares and log2 / exp2 at one ulp each (the log's absolute error times 0.75)
+    assert float(((out - ref).abs() - (half_ulp + 2e-6) * ref.abs()).max()) <= (1e-7 if dt == "f16" else 0)
+
+
+@pytest.mark.parametrize("dt", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("C,shape", [(8, (2, 3, 2)), (2048, (1, 4, 5)), (2560, (1, 5, 2))])
+def test_maxpool_channel_counts(D, dt, C, shape):
+    if dt == "f32":
+        C //= 2
+    g = torch.Generator().manual_seed(C)
+    x = torch.randn((*shape, C), generator=g).to(TORCH_DT[dt])
+    out = D.densenet_maxpool(x.cuda(), DTS[dt]).float().cpu()
+    ref = torch.nn.functional.max_pool2d(x.float().permute(0, 3, 1, 2), 3, 2, ceil_mode=True)
+    assert torch.equal(out, ref.permute(0, 2, 3, 1))
