@@ -110,11 +110,12 @@ int launch_warp_regions(const uint8_t* d_img, int32_t n_img, int32_t H, int32_t 
                         const int32_t* d_box_img, int32_t n, int32_t S, int32_t pitch, const float* mean,
                         dn_dtype dt, void* d_out, void* stream);
 
-// Packed weight blob: offsets in bytes of each layer's weights and fp32 biases, and (16-bit types)
-// of a second, stage-major copy of the weights that the direct-load conv kernels stream as
-// contiguous blocks (0 when absent).
+// Packed weight blob: offsets in bytes of each layer's weights and fp32 biases, and of a second,
+// stage-major copy of the weights that the direct-load conv kernels stream as contiguous blocks (0 when
+// absent; fp32: three bf16 parts of each weight).  special_off (fp32): a word per layer, non-zero when a
+// weight has no such parts (an infinity, a NaN or a value beyond bf16's range).
 struct PackedLayout {
-  size_t w_off[5], b_off[5], s_off[5], total;
+  size_t w_off[5], b_off[5], s_off[5], special_off, total;
 };
 PackedLayout packed_layout(dn_dtype dt);
 int launch_pack_weights(const float* const* d_w, const float* const* d_b, dn_dtype dt, void* d_packed,
@@ -257,9 +258,9 @@ class TraceScope {
 #if defined(__HIPCC__)
 namespace dn {
 // ---------------------------------------------------------------------------------------------
-// Device side: storage types and the gfx950 MFMA tiles used by the conv kernels.
+// Device side: storage types and the gfx950 MFMA tile used by the conv kernels.
 //   32x32x16 f16 / bf16: each lane holds 8 consecutive k of row (lane % 32) of A and column
-//   (lane % 32) of B, k offset 8 * (lane / 32); 32x32x2 f32: one k, offset lane / 32.  The
+//   (lane % 32) of B, k offset 8 * (lane / 32).  The
 //   accumulator register r of lane l holds D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
 // ---------------------------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -273,7 +274,6 @@ template <typename T>
 struct Mfma;
 template <>
 struct Mfma<_Float16> {
-  static constexpr int KPL = 8, KS = 16;
   typedef f16x8 frag;
   typedef f16x4 half_frag;
   __device__ static inline f32x16 mma(frag a, frag b, f32x16 c) {
@@ -282,23 +282,12 @@ struct Mfma<_Float16> {
 };
 template <>
 struct Mfma<__bf16> {
-  static constexpr int KPL = 8, KS = 16;
   typedef bf16x8 frag;
   typedef bf16x4 half_frag;
   __device__ static inline f32x16 mma(frag a, frag b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
 };
-template <>
-struct Mfma<float> {
-  static constexpr int KPL = 1, KS = 2;
-  typedef float frag;
-  typedef float half_frag;
-  __device__ static inline f32x16 mma(frag a, frag b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
-};
-
 template <typename T>
 __device__ inline T from_f32(float x) {
   return (T)x;  // round to nearest even for _Float16 and __bf16

@@ -1,6 +1,6 @@
 // Convolution engine for conv1..conv5 of the AlexNet topology (the bulk of the path's work, Sec. 3),
-// as implicit GEMMs on gfx950 MFMA: fp16 / bf16 inputs with fp32 accumulation (32x32x16 tiles) or an
-// fp32 path (32x32x2 tiles).  Bias and ReLU are applied in the epilogue.
+// as implicit GEMMs on gfx950 MFMA (32x32x16 tiles, fp32 accumulation): fp16 / bf16 inputs, or fp32 inputs
+// as three bf16 parts each.  Bias and ReLU are applied in the epilogue.
 //
 // GEMM view: rows = output pixels of a 2-D spatial tile, columns = output channels of one group,
 // k = (input channel, kernel tap).  A workgroup stages the input tile with its halo in LDS once per
@@ -32,6 +32,9 @@ namespace {
 //          contiguous block of R * BM * 2 16-byte pieces, piece (kx BM + m) 2 + p holding input
 //          channels 8 (p ^ ((m >> 4) & 1)) .. + 7 of the chunk at tap (ky, kx) of channel m: exactly
 //          the order of the LDS weight-row buffer, so each direct load reads 1 KB of contiguous memory
+//   conv1..5, fp32: split copies for conv1_f32_kernel and conv_f32_kernel, three bf16 parts of each weight:
+//          per channel block of 64, chunk of 16 input channels and tap (conv1: per input channel and
+//          k-step, all 96 channels) [3][channels][2 slots of 8 k], the slots swapped as above
 //   biases: fp32 [M]
 // ------------------------------------------------------------------------------------------------
 constexpr int L_M[5] = {96, 256, 384, 384, 256};
@@ -112,142 +115,74 @@ __global__ void pack_stage_kernel(const float* __restrict__ w, T* __restrict__ o
   out[i] = from_f32<T>(w[((oc * Cg + c) * R + ky) * R + kx]);
 }
 
+// Bits of |x| from which x rounds to a bf16 infinity (or is one, or a NaN).
+constexpr uint32_t SPLIT_LIMIT = 0x7f7f8000u;
+
+// x = h + m + l, each the nearest bf16 of the rest.
+struct Split3 {
+  __bf16 h, m, l;
+};
+__device__ inline Split3 split3(float x) {
+  Split3 s;
+  s.h = (__bf16)x;
+  const float r = x - (float)s.h;
+  s.m = (__bf16)r;
+  s.l = (__bf16)(r - (float)s.m);
+  return s;
+}
+
+// conv2..5, fp32 storage: the stage-major copy for conv_f32_kernel, one thread per weight.  Per channel
+// block (group, 64 output channels), chunk of 16 input channels and tap: the weights' three bf16 parts
+// [3][64][2 slots], the slots swapped for channels 16..31 of every 32.  *special is set when a weight does
+// not split.
+__global__ void pack_split_kernel(const float* __restrict__ w, __bf16* __restrict__ out,
+                                  uint32_t* __restrict__ special, int Mg, int Cg, int RR, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int c = (int)(i % 16), m = (int)((i / 16) % 64);
+  const int64_t r = i / (16 * 64);  // (block, chunk, tap)
+  const int tap = (int)(r % RR), nchunks = Cg / 16, chunk = (int)((r / RR) % nchunks);
+  const int64_t blk = r / RR / nchunks;
+  const int64_t oc = blk * 64 + m;  // blocks run through the groups' channels in order
+  const float x = w[(oc * Cg + chunk * 16 + c) * RR + tap];
+  if ((__builtin_bit_cast(uint32_t, x) & 0x7fffffffu) >= SPLIT_LIMIT) atomicOr(special, 1u);
+  const Split3 s = split3(x);
+  __bf16* d = out + r * (3 * 64 * 16) + m * 16 + ((c >> 3) ^ ((m >> 4) & 1)) * 8 + (c & 7);
+  d[0] = s.h;
+  d[64 * 16] = s.m;
+  d[2 * 64 * 16] = s.l;
+}
+
+// conv1, fp32 storage: per input channel and k-step (K1's order) the weights' three bf16 parts [3][96][2
+// slots], the slots swapped for channels 16..31 of every 32.
+__global__ void pack_split1_kernel(const float* __restrict__ w, __bf16* __restrict__ out,
+                                   uint32_t* __restrict__ special) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= 3 * K1 * 96) return;
+  const int kk = i % 16, m = (i / 16) % 96, cs = i / (16 * 96);  // cs = channel * 9 + k-step
+  const int c = cs / (K1 / 16), k = (cs % (K1 / 16)) * 16 + kk, ky = conv1_ky(k), kx = conv1_kx(k);
+  const float x = ky < 11 && kx < 11 ? w[((m * 3 + c) * 11 + ky) * 11 + kx] : 0.f;
+  if ((__builtin_bit_cast(uint32_t, x) & 0x7fffffffu) >= SPLIT_LIMIT) atomicOr(special, 1u);
+  const Split3 s = split3(x);
+  __bf16* d = out + cs * (3 * 96 * 16) + m * 16 + ((kk >> 3) ^ ((m >> 4) & 1)) * 8 + (kk & 7);
+  d[0] = s.h;
+  d[96 * 16] = s.m;
+  d[2 * 96 * 16] = s.l;
+}
+
+__global__ void clear_words_kernel(uint32_t* p, int n) {
+  if ((int)threadIdx.x < n) p[threadIdx.x] = 0u;
+}
+
 __global__ void copy_f32_kernel(const float* __restrict__ a, float* __restrict__ b, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) b[i] = a[i];
 }
 
-// ------------------------------------------------------------------------------------------------
-// LDS fragment loads
-// ------------------------------------------------------------------------------------------------
+// One 16-byte LDS fragment: 8 consecutive 16-bit values.
 template <typename T>
-__device__ inline typename Mfma<T>::frag lds_frag16(const T* p) {  // 8 consecutive halves, 16 B
+__device__ inline typename Mfma<T>::frag lds_frag16(const T* p) {
   return *(const typename Mfma<T>::frag*)p;
-}
-template <>
-__device__ inline float lds_frag16<float>(const float* p) {
-  return *p;
-}
-
-// ------------------------------------------------------------------------------------------------
-// conv1: 11x11 / stride 4 / no padding, 3 -> 96 channels, channel-major input planes.
-// Workgroup: 16 x 16 output pixels x all 96 output channels, 4 waves of 96 channels x 64 pixels.
-// ------------------------------------------------------------------------------------------------
-template <typename T>
-struct Conv1Cfg {
-  static_assert(std::is_same<T, float>::value, "16-bit storage uses the direct or persistent kernel");
-  static constexpr int TH = 16, TW = 16;
-  static constexpr int HR = 72;  // halo rows / cols (4*15+12)
-  static constexpr int HS = 72;  // halo row stride
-  static constexpr int WS = K1 + 1;
-};
-
-// ksplit > 1: as conv_s1_kernel's split, over the three input channels.
-template <typename T>
-__global__ __launch_bounds__(256) void conv1_kernel(const T* __restrict__ in, T* __restrict__ out,
-                                                    const T* __restrict__ wp,
-                                                    const float* __restrict__ bias, KRuns runs,
-                                                    int ksplit, int base, float* __restrict__ part,
-                                                    int64_t part_slice) {
-  using C = Conv1Cfg<T>;
-  using Op = Mfma<T>;
-  __shared__ T s_in[C::HR * C::HS];
-  __shared__ T s_w[96 * C::WS];
-
-  int bid = blockIdx.x;
-  const int copy = bid / base;  // split copy: input channels [3 copy / ksplit, 3 (copy + 1) / ksplit)
-  bid -= copy * base;
-  const KRun& rn = runs.r[run_of(runs, bid)];
-  bid -= rn.first;
-  const int H = rn.H, W = rn.W, tiles_x = rn.tiles_x, tiles_y = rn.tiles_y;
-  const int64_t in_stride = rn.in_stride, out_stride = rn.out_stride;
-  in += rn.in_off;
-  out += rn.out_off;
-  const int P = rn.pitch, Ho = rn.Ho, Wo = rn.Wo;
-  const int tx = bid % tiles_x;
-  bid /= tiles_x;
-  const int ty = bid % tiles_y;
-  const int plane = bid / tiles_y;
-  const int oy0 = ty * C::TH, ox0 = tx * C::TW;
-  const int iy0 = oy0 * 4, ix0 = ox0 * 4;
-  const T* src = in + plane * in_stride;
-
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int half = lane >> 5, l32 = lane & 31;
-  int prow[2], pcol[2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int idx = wave * 64 + t * 32 + l32;
-    prow[t] = idx / C::TW;
-    pcol[t] = idx % C::TW;
-  }
-  f32x16 acc[3][2];
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int t = 0; t < 2; ++t) acc[a][t] = f32x16{};
-
-  for (int c = copy * 3 / ksplit; c < (copy + 1) * 3 / ksplit; ++c) {
-    __syncthreads();
-    const T* sc = src + (int64_t)c * H * P;
-    for (int e = threadIdx.x; e < C::HR * C::HR; e += 256) {
-      const int hy = e / C::HR, hx = e % C::HR;
-      const int iy = iy0 + hy, ix = ix0 + hx;
-      T v = from_f32<T>(0.f);
-      if (iy < H && ix < W) v = sc[(int64_t)iy * P + ix];
-      s_in[hy * C::HS + hx] = v;
-    }
-    for (int e = threadIdx.x; e < 96 * K1; e += 256) {
-      const int m = e / K1, k = e % K1;
-      s_w[m * C::WS + k] = wp[(m * 3 + c) * K1 + k];
-    }
-    __syncthreads();
-#pragma unroll 3
-    for (int ks = 0; ks < K1 / Op::KS; ++ks) {
-      typename Op::frag a[2], b[3];
-      const int k = ks * 2 + half, ky = conv1_ky(k), kx = conv1_kx(k);
-#pragma unroll
-      for (int t = 0; t < 2; ++t) a[t] = s_in[(4 * prow[t] + ky) * C::HS + 4 * pcol[t] + kx];
-#pragma unroll
-      for (int mt = 0; mt < 3; ++mt) b[mt] = s_w[(mt * 32 + l32) * C::WS + k];
-#pragma unroll
-      for (int mt = 0; mt < 3; ++mt)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) acc[mt][t] = Op::mma(a[t], b[mt], acc[mt][t]);
-    }
-  }
-
-  if (ksplit > 1) {  // raw partial sums of this split
-    float* pd = part + copy * part_slice + rn.out_off + plane * out_stride;
-#pragma unroll
-    for (int mt = 0; mt < 3; ++mt)
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int i = 8 * (r >> 2) + 4 * half + (r & 3);
-          const int idx = wave * 64 + t * 32 + i;
-          const int oy = oy0 + idx / C::TW, ox = ox0 + idx % C::TW;
-          if (oy < Ho && ox < Wo) pd[((int64_t)oy * Wo + ox) * 96 + mt * 32 + l32] = acc[mt][t][r];
-        }
-    return;
-  }
-  T* dst = out + plane * out_stride;
-#pragma unroll
-  for (int mt = 0; mt < 3; ++mt) {
-    const int m = mt * 32 + l32;
-    const float bv = bias[m];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = 8 * (r >> 2) + 4 * half + (r & 3);
-        const int idx = wave * 64 + t * 32 + i;
-        const int oy = oy0 + idx / C::TW, ox = ox0 + idx % C::TW;
-        if (oy < Ho && ox < Wo)
-          dst[((int64_t)oy * Wo + ox) * 96 + m] = from_f32<T>(fmaxf(acc[mt][t][r] + bv, 0.f));
-      }
-  }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -410,16 +345,11 @@ int device_cu_count() {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Stride-1 R x R conv with zero padding (R-1)/2, grouped, channels-last.
-// Workgroup: TH x TW = 16 x 16 output pixels x BM output channels of one group.  Waves: BM/(32 TM)
-// along channels x 2 along pixels; each wave owns 32 TM channels x 128 pixels (TM x 4 MFMA tiles).  The MFMA
-// A operand is the weights and B the pixels, so each lane's accumulator holds 4 consecutive output
-// channels of one pixel per register group and the epilogue stores 4 channels at a time.
-// Pipeline: a stage is (chunk of 16 input channels, kernel row ky).  LDS holds two halo buffers
-// ((TH+R-1) x (TW+R-1) x 16 channels, one per chunk) and two weight-row buffers (R taps x BM x 16).
-// While a stage computes from LDS, the next stage's weight row (and, during a chunk's first row, the
-// next chunk's halo) is already in flight into registers; it is written to the other buffers after
-// the stage's MFMAs, and one barrier per stage publishes it.
+// Stride-1 R x R conv with zero padding (R-1)/2, grouped, channels-last: the tile geometry and LDS layout
+// the kernels below share.
+// Workgroup: TH x TW output pixels x BM output channels of one group.  The MFMA A operand is the
+// weights and B the pixels, so each lane's accumulator holds 4 consecutive output channels of one pixel
+// per register group.  LDS holds halos ((TH+R-1) x (TW+R-1) pixels) of 16 input channels at a time.
 // ------------------------------------------------------------------------------------------------
 // Slots (16 bytes) that collide modulo 512 bytes when the 32 lanes of a half-wave read pixels
 // (r, c), r < 16, c < 2, of a halo whose rows are rs slots apart (two slots per pixel).
@@ -441,33 +371,25 @@ constexpr int halo_row_pad(int hw) {
 
 template <typename T, int R, int BM, int TM, int TS, int TN_ = 4>
 struct ConvCfg {
-  // Tile of TH x TW output pixels, TS = 100 TH + TW (TW 16 or 32, TH TW a multiple of 256) for 16-bit
-  // storage; fp32 uses 16 x 16.
-  static constexpr bool F32_ = std::is_same<T, float>::value;
-  static constexpr int TH = F32_ ? 16 : TS / 100, TW = F32_ ? 16 : TS % 100, CC = 16;
+  // Tile of TH x TW output pixels, TS = 100 TH + TW (TW 16 or 32, TH TW a multiple of 256).
+  static constexpr int TH = TS / 100, TW = TS % 100, CC = 16;
+  static_assert(sizeof(T) == 2, "MFMA operands are 16-bit");
   static_assert((TW == 16 || TW == 32) && TH % 2 == 0 && (TH * TW) % 256 == 0, "tile shape");
   static constexpr int TN = TN_;                   // 32-pixel MFMA tiles per wave (32 TN pixels)
   static constexpr int HH = TH + R - 1, HW = TW + R - 1;
-  static constexpr bool F32 = std::is_same<T, float>::value;
   static constexpr int WM = BM / (32 * TM), WN = (TH * TW) / (32 * TN);
   static constexpr int NT = 64 * WM * WN;
-  static constexpr int VEC = 16 / sizeof(T);  // elements per 16-byte global load
-  static constexpr int VPP = CC / VEC;
-  static constexpr int HALO_V = HH * HW * VPP, HALO_PER = (HALO_V + NT - 1) / NT;
-  static constexpr int W_V = R * BM * VPP, W_PER = (W_V + NT - 1) / NT;
+  static constexpr int VEC = 8;                    // elements per 16-byte slot
   static_assert(WM * 32 * TM == BM, "channel block must be whole wave tiles");
-  // LDS layout.  16-bit types: a pixel (or an output channel's weight row) is 32 bytes, two 16-byte
-  // slots.  The 32 lanes of a half-wave read 16 bytes each and must hit distinct slots modulo 512
-  // bytes: a halo row is padded by an odd number of slots (RP), so the two tile rows a half-wave
-  // reads land on slots of opposite parity; the weight rows of channels 16..31 of a 32-channel group
-  // swap their two slots.  fp32: a pixel or channel row is CC + 1 floats.
-  static constexpr int PS = F32 ? CC + 1 : CC;          // pixel stride (elements)
-  static constexpr int RP = F32 ? 0 : halo_row_pad(HW);  // halo row padding (16-byte slots)
-  static constexpr int RSS = 2 * HW + RP;                // 16-bit halo row stride (slots)
-  static constexpr int RS = F32 ? HW * PS : HW * PS + 8 * RP;  // halo row stride (elements)
-  static constexpr int HALO_E = HH * RS, W_E = R * BM * PS;
-  static constexpr int STAGE_E = F32 ? 0 : WM * WN * 32 * TN * 64;  // epilogue staging
-  static constexpr int LDS_E = (2 * HALO_E + 2 * W_E) > STAGE_E ? (2 * HALO_E + 2 * W_E) : STAGE_E;
+  // LDS layout.  A pixel (or an output channel's weight row) is 32 bytes, two 16-byte slots.  The 32
+  // lanes of a half-wave read 16 bytes each and must hit distinct slots modulo 512 bytes: a halo row
+  // is padded by an odd number of slots (RP), so the two tile rows a half-wave reads land on slots of
+  // opposite parity; the weight rows of channels 16..31 of a 32-channel group swap their two slots.
+  static constexpr int PS = CC;                         // pixel stride (elements)
+  static constexpr int RP = halo_row_pad(HW);           // halo row padding (16-byte slots)
+  static constexpr int RSS = 2 * HW + RP;               // halo row stride (slots)
+  static constexpr int RS = HW * PS + 8 * RP;           // halo row stride (elements)
+  static constexpr int STAGE_E = WM * WN * 32 * TN * 64;  // epilogue staging of 64 channels per wave
   __device__ static inline int halo_off(int hy, int hx, int v) { return hy * RS + hx * PS + v * VEC; }
   // Tile pixel of index idx: each 32-pixel MFMA tile is 2 rows x 16 columns (the two rows a half-wave
   // reads then fall on LDS slots of opposite parity); with 32-column tiles, MFMA tiles 2 p and 2 p + 1
@@ -475,273 +397,13 @@ struct ConvCfg {
   __device__ static inline int pix_row(int idx) { return 2 * ((idx >> 5) / (TW / 16)) + ((idx >> 4) & 1); }
   __device__ static inline int pix_col(int idx) { return 16 * ((idx >> 5) % (TW / 16)) + (idx & 15); }
   __device__ static inline int w_off(int kx, int m, int v) {
-    return (kx * BM + m) * PS + (F32 ? v * VEC : ((v ^ ((m >> 4) & 1)) * VEC));
+    return (kx * BM + m) * PS + (v ^ ((m >> 4) & 1)) * VEC;
   }
 };
 
 template <typename T, int BM, int TM, int TS, int TN = 4>
 constexpr int conv_threads() {
-  return 64 * (BM / (32 * TM)) * (std::is_same<T, float>::value ? 256 : (TS / 100) * (TS % 100)) / (32 * TN);
-}
-
-// ksplit > 1 (fp32 launches too small to fill the chip): the launch is ksplit copies of its base
-// workgroups; copy ks runs the input-channel chunks [ks nchunks / ksplit, (ks + 1) nchunks / ksplit)
-// and writes its raw sums (no bias, no ReLU) to part + ks part_slice at the output's element offsets;
-// split_reduce_kernel then adds the copies in order.
-// (fp32 instances run one wave per SIMD whatever the configuration asks: their registers need it)
-template <typename T, int OCC>
-constexpr int conv_s1_occ() {
-  return std::is_same<T, float>::value ? 1 : OCC;
-}
-
-template <typename T, int R, int BM, int TM, int OCC, int TS>
-__global__ __launch_bounds__((conv_threads<T, BM, TM, TS>()), (conv_s1_occ<T, OCC>())) void conv_s1_kernel(
-    const T* __restrict__ in, T* __restrict__ out, const T* __restrict__ wp,
-    const float* __restrict__ bias, KRuns runs, int C, int Cg, int M, int Mg, int mblocks, int ksplit,
-    int base, float* __restrict__ part, int64_t part_slice) {
-  using Cf = ConvCfg<T, R, BM, TM, TS>;
-  using Op = Mfma<T>;
-  constexpr int pad = (R - 1) / 2;
-  constexpr int VEC = Cf::VEC, VPP = Cf::VPP, NT = Cf::NT, TN = Cf::TN;
-  typedef T vec_t __attribute__((ext_vector_type(VEC)));
-  typedef T out4_t __attribute__((ext_vector_type(4)));
-  constexpr int HALO_E = Cf::HALO_E, W_E = Cf::W_E;
-  __shared__ __align__(16) T s_mem[Cf::LDS_E];
-  auto halo_buf = [&](int b) { return s_mem + b * HALO_E; };
-  auto wrow_buf = [&](int b) { return s_mem + 2 * HALO_E + b * W_E; };
-
-  // XCD-aware order: workgroups are dispatched round-robin over the 8 XCDs, so the i-th block of XCD
-  // x takes logical index x * (blocks per XCD) + i; consecutive logical blocks (the channel blocks of
-  // one tile first, then neighbouring tiles) then share that XCD's L2.
-  const int nb = gridDim.x, xcd = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
-  int bid = xcd * per + min(xcd, rem) + blockIdx.x / 8;
-  const int ks = bid / base;
-  bid -= ks * base;
-  const KRun& rn = runs.r[run_of(runs, bid)];
-  bid -= rn.first;
-  const int H = rn.H, W = rn.W, tiles_x = rn.tiles_x, tiles_y = rn.tiles_y;
-  const int64_t in_stride = rn.in_stride, out_stride = rn.out_stride;
-  in += rn.in_off;
-  out += rn.out_off;
-  const int mb = bid % mblocks;
-  bid /= mblocks;
-  const int tx = bid % tiles_x;
-  bid /= tiles_x;
-  const int ty = bid % tiles_y;
-  const int plane = bid / tiles_y;
-  const int mpg = Mg / BM;
-  const int g = mb / mpg, m0 = (mb % mpg) * BM;
-  const int oy0 = ty * Cf::TH, ox0 = tx * Cf::TW;
-  const T* src = in + plane * in_stride + g * Cg;
-  const T* wg = wp + ((int64_t)g * Mg + m0) * R * R * Cg;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave % Cf::WM, wn = wave / Cf::WM;
-  const int half = lane >> 5, l32 = lane & 31;
-  int pix[TN];  // LDS element offset of this lane's pixel (tap 0, 0) in each pixel tile
-#pragma unroll
-  for (int t = 0; t < TN; ++t) {
-    const int idx = wn * 32 * TN + t * 32 + l32;
-    pix[t] = Cf::halo_off(Cf::pix_row(idx), Cf::pix_col(idx), 0);
-  }
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int a = 0; a < TM; ++a)
-#pragma unroll
-    for (int t = 0; t < TN; ++t) acc[a][t] = f32x16{};
-
-  vec_t hreg[Cf::HALO_PER], wreg[Cf::W_PER];
-  auto load_halo = [&](int c0) {
-#pragma unroll
-    for (int i = 0; i < Cf::HALO_PER; ++i) {
-      const int e = tid + i * NT;
-      vec_t val = vec_t{};
-      if (e < Cf::HALO_V) {
-        const int v = e % VPP, p = e / VPP;
-        const int iy = oy0 - pad + p / Cf::HW, ix = ox0 - pad + p % Cf::HW;
-        if (iy >= 0 && iy < H && ix >= 0 && ix < W)
-          val = *(const vec_t*)(src + ((int64_t)iy * W + ix) * C + c0 + v * VEC);
-      }
-      hreg[i] = val;
-    }
-  };
-  auto store_halo = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < Cf::HALO_PER; ++i) {
-      const int e = tid + i * NT;
-      if (e < Cf::HALO_V) {
-        const int p = e / VPP;
-        T* d = halo_buf(buf) + Cf::halo_off(p / Cf::HW, p % Cf::HW, e % VPP);
-        if constexpr (Cf::F32) {
-#pragma unroll
-          for (int q = 0; q < VEC; ++q) d[q] = hreg[i][q];
-        } else {
-          *(vec_t*)d = hreg[i];
-        }
-      }
-    }
-  };
-  auto load_w = [&](int c0, int ky) {
-#pragma unroll
-    for (int i = 0; i < Cf::W_PER; ++i) {
-      const int e = tid + i * NT;
-      vec_t val = vec_t{};
-      if (e < Cf::W_V) {
-        const int v = e % VPP, t = e / VPP;
-        const int m = t % BM, kx = t / BM;
-        val = *(const vec_t*)(wg + ((int64_t)m * R * R + ky * R + kx) * Cg + c0 + v * VEC);
-      }
-      wreg[i] = val;
-    }
-  };
-  auto store_w = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < Cf::W_PER; ++i) {
-      const int e = tid + i * NT;
-      if (e < Cf::W_V) {
-        const int v = e % VPP, t = e / VPP;
-        const int m = t % BM, kx = t / BM;
-        T* d = wrow_buf(buf) + Cf::w_off(kx, m, v);
-        if constexpr (Cf::F32) {
-#pragma unroll
-          for (int q = 0; q < VEC; ++q) d[q] = wreg[i][q];
-        } else {
-          *(vec_t*)d = wreg[i];
-        }
-      }
-    }
-  };
-  auto compute = [&](int hb, int wb, int ky) {
-    const T* hs = halo_buf(hb);
-    const T* ws = wrow_buf(wb);
-#pragma unroll
-    for (int kx = 0; kx < R; ++kx) {
-#pragma unroll
-      for (int kk = 0; kk < Cf::CC / Op::KS; ++kk) {
-        const int koff = kk * Op::KS + half * Op::KPL;
-        typename Op::frag x[TN], w[TM];
-        // k offset of this lane: element koff of the 16-channel chunk (16-bit: slot `half`)
-#pragma unroll
-        for (int t = 0; t < TN; ++t)
-          x[t] = lds_frag16<T>(hs + pix[t] + ky * Cf::RS + kx * Cf::PS + koff);
-#pragma unroll
-        for (int mt = 0; mt < TM; ++mt) {
-          const int m = wm * 32 * TM + mt * 32 + l32;
-          if constexpr (Cf::F32)
-            w[mt] = lds_frag16<T>(ws + Cf::w_off(kx, m, 0) + koff);
-          else
-            w[mt] = lds_frag16<T>(ws + Cf::w_off(kx, m, half));
-        }
-#pragma unroll
-        for (int mt = 0; mt < TM; ++mt)
-#pragma unroll
-          for (int t = 0; t < TN; ++t) acc[mt][t] = Op::mma(w[mt], x[t], acc[mt][t]);
-      }
-    }
-  };
-
-  // this workgroup's chunks [c_lo, c_hi) (all of them without a split): stages c_lo R .. c_hi R - 1
-  const int nchunks = Cg / Cf::CC;
-  const int c_lo = ks * nchunks / ksplit, c_hi = (ks + 1) * nchunks / ksplit;
-  const int st0 = c_lo * R, st1 = c_hi * R;
-  load_halo(c_lo * Cf::CC);
-  load_w(c_lo * Cf::CC, 0);
-  store_halo(c_lo & 1);
-  store_w(st0 & 1);
-  __syncthreads();
-  for (int st = st0; st < st1; ++st) {
-    const int chunk = st / R, ky = st - chunk * R;
-    const bool more = st + 1 < st1, next_chunk = chunk + 1 < c_hi;
-    if (more) load_w(((st + 1) / R) * Cf::CC, (st + 1) % R);
-    if (ky == 0 && next_chunk) load_halo((chunk + 1) * Cf::CC);
-    compute(chunk & 1, st & 1, ky);
-    if (more) store_w((st + 1) & 1);
-    if (ky == R - 1 && next_chunk) store_halo((chunk + 1) & 1);
-    __syncthreads();
-  }
-
-  if constexpr (Cf::F32) {
-    if (ksplit > 1) {  // raw partial sums of this split
-      float* pd = part + ks * part_slice + rn.out_off + plane * out_stride;
-#pragma unroll
-      for (int mt = 0; mt < TM; ++mt)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int m = g * Mg + m0 + wm * 32 * TM + mt * 32 + 8 * q + 4 * half;
-#pragma unroll
-          for (int t = 0; t < TN; ++t) {
-            const int idx = wn * 32 * TN + t * 32 + l32;
-            const int oy = oy0 + Cf::pix_row(idx), ox = ox0 + Cf::pix_col(idx);
-            if (oy < H && ox < W) {
-              f32x4 r;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) r[e] = acc[mt][t][4 * q + e];
-              *(f32x4*)(pd + ((int64_t)oy * W + ox) * M + m) = r;
-            }
-          }
-        }
-      return;
-    }
-  }
-
-  // Epilogue: D[m][pixel]; register group q of MFMA tile mt holds channels 32 mt + 8 q + 4 half + 0..3
-  // of pixel l32.
-  T* dst = out + plane * out_stride;
-  if constexpr (!Cf::F32 && TM == 2) {
-    // Stage each wave's 128 pixels x 64 channels (one 128-byte line per pixel) in LDS, 16-byte chunks
-    // XOR-swizzled by the pixel index, then write whole lines: 8 lanes per pixel, 16 bytes each.
-    typedef T vec8_t __attribute__((ext_vector_type(8)));
-    static_assert(Cf::STAGE_E <= Cf::LDS_E, "staging must fit in LDS");
-    T* stg = s_mem + wave * (32 * TN * 64);
-#pragma unroll
-    for (int mt = 0; mt < TM; ++mt)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int j = 4 * mt + q;
-        const f32x4 bv = *(const f32x4*)(bias + g * Mg + m0 + wm * 64 + 8 * j + 4 * half);
-#pragma unroll
-        for (int t = 0; t < TN; ++t) {
-          const int p = t * 32 + l32;
-          out4_t r;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) r[e] = from_f32<T>(fmaxf(acc[mt][t][4 * q + e] + bv[e], 0.f));
-          const int key = (p & 7) ^ ((p >> 3) & 3);
-          *(out4_t*)(stg + p * 64 + ((j ^ key) * 8) + 4 * half) = r;
-        }
-      }
-    __syncthreads();
-    const int j = lane & 7;
-#pragma unroll
-    for (int it = 0; it < (32 * TN) / 8; ++it) {
-      const int p = it * 8 + (lane >> 3);
-      const int key = (p & 7) ^ ((p >> 3) & 3);
-      const vec8_t v = *(const vec8_t*)(stg + p * 64 + ((j ^ key) * 8));
-      const int idx = wn * 32 * TN + p;
-      const int oy = oy0 + Cf::pix_row(idx), ox = ox0 + Cf::pix_col(idx);
-      if (oy < H && ox < W)
-        *(vec8_t*)(dst + ((int64_t)oy * W + ox) * M + g * Mg + m0 + wm * 64 + 8 * j) = v;
-    }
-  } else {
-#pragma unroll
-    for (int mt = 0; mt < TM; ++mt)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int m = g * Mg + m0 + wm * 32 * TM + mt * 32 + 8 * q + 4 * half;
-        const f32x4 bv = *(const f32x4*)(bias + m);
-#pragma unroll
-        for (int t = 0; t < TN; ++t) {
-          const int idx = wn * 32 * TN + t * 32 + l32;
-          const int oy = oy0 + Cf::pix_row(idx), ox = ox0 + Cf::pix_col(idx);
-          if (oy < H && ox < W) {
-            out4_t r;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) r[e] = from_f32<T>(fmaxf(acc[mt][t][4 * q + e] + bv[e], 0.f));
-            *(out4_t*)(dst + ((int64_t)oy * W + ox) * M + m) = r;
-          }
-        }
-      }
-  }
+  return 64 * (BM / (32 * TM)) * (TS / 100) * (TS % 100) / (32 * TN);
 }
 
 // Sum of the ksplit partial copies of a split fp32 conv launch, in copy order, plus bias, then ReLU:
@@ -769,12 +431,15 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const float* __restri
 }
 
 // ------------------------------------------------------------------------------------------------
-// Stride-1 conv for 16-bit storage with direct global->LDS loads.  Same tiling, stages, LDS layout and
-// epilogue as conv_s1_kernel, but every stage buffer is filled by buffer_load_dwordx4 ... lds: one
-// wave instruction writes 64 consecutive 16-byte LDS slots, each lane choosing the global address of
-// its slot (padding slots and halo pixels outside the map use an offset past the buffer's end, which
-// the hardware returns as zeros).  No registers hold staged data and no LDS store instructions are
-// issued; a stage's loads are waited for (vmcnt) just before the barrier that publishes them.
+// Stride-1 conv for 16-bit storage with direct global->LDS loads.  Waves: BM/(32 TM) along channels x
+// (TH TW)/(32 TN) along pixels.  Pipeline: a stage is (chunk of 16 input channels, kernel row ky).  LDS
+// holds two halo buffers (one per chunk) and two weight-row buffers (R taps x BM x 16).  While a stage
+// computes, the next stage's weight row (and, during a chunk's first row, the next chunk's halo) is
+// loaded by buffer_load_dwordx4 ... lds: one wave instruction writes 64 consecutive 16-byte LDS slots,
+// each lane choosing the global address of its slot (padding slots and halo pixels outside the map use
+// an offset past the buffer's end, which the hardware returns as zeros).  No registers hold staged data
+// and no LDS store instructions are issued; a stage's loads are waited for (vmcnt) just before the
+// barrier that publishes them.
 // ------------------------------------------------------------------------------------------------
 template <int BYTES>
 struct Pieces {  // 1 KB LDS pieces, rounded up to a whole number per wave
@@ -813,7 +478,7 @@ __global__ __launch_bounds__((conv_threads<T, BM, TM, TS, TN_>()), OCC) void con
     const float* __restrict__ bias, KRuns runs, int C, int Cg, int M, int Mg, int mblocks) {
   using Cf = ConvCfg<T, R, BM, TM, TS, TN_>;
   using Op = Mfma<T>;
-  static_assert(!Cf::F32 && (TM == 2 || TM == 3), "direct-load path is for 16-bit storage");
+  static_assert(TM == 2 || TM == 3, "epilogues for 64 or 96 channels per wave");
   constexpr int pad = (R - 1) / 2;
   constexpr int TN = Cf::TN, NW = Cf::WM * Cf::WN;
   static_assert(BMP % BM == 0, "a channel block is a sub-block of the weight copy's block");
@@ -986,7 +651,8 @@ __global__ __launch_bounds__((conv_threads<T, BM, TM, TS, TN_>()), OCC) void con
   typedef T vec8_t __attribute__((ext_vector_type(8)));
   T* dst = out + plane * out_stride;
   if constexpr (TM == 2) {
-    // Epilogue as in conv_s1_kernel: stage 128 pixels x 64 channels per wave, write whole lines.
+    // Epilogue: stage each wave's pixels x 64 channels (one 128-byte line per pixel) in LDS, 16-byte
+    // chunks XOR-swizzled by the pixel index, then write whole lines: 8 lanes per pixel.
     constexpr int WPR = NW / ROUNDS;  // waves staging per round
   #pragma unroll
     for (int round = 0; round < ROUNDS; ++round) {
@@ -1061,6 +727,556 @@ __global__ __launch_bounds__((conv_threads<T, BM, TM, TS, TN_>()), OCC) void con
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Stride-1 conv for fp32 storage on the bf16 matrix cores.  An fp32 value is split into three bf16
+// values, x = h + m + l + d with |d| <= 2^-27 |x| (each the nearest bf16 of what is left), and a product
+// x w is h h' + (h m' + m h') + (m m' + h l' + l h'): the dropped terms are below 2^-25 |x w| and of
+// both signs, less than the half ulp an fp32 product is off by.  Six bf16 MFMAs replace eight fp32 ones
+// of the same k, and run at 16 times their rate.  h h' and the five small terms are summed in
+// accumulators of their own, so the sum of the large terms is rounded once per 16 k (the fp32 MFMA
+// rounds it once per 2 k).
+// Values that do not split (infinities, NaN, and finite values that round to a bf16 infinity) are seen
+// as they are staged (inputs) or packed (weights); a workgroup that meets one computes its outputs
+// again from the fp32 data with scalar FMAs, which follow the fp32 rules.
+//
+// Workgroup: 16 x 16 output pixels x 64 channels of one group, four waves of 64 channels x 64 pixels.
+// LDS holds one halo of 16 input channels as three bf16 planes, and two buffers of three taps' weights,
+// streamed by direct loads from the split copy.  The next chunk's halo is loaded into registers while
+// a chunk computes and is split between two barriers at its end.  72 MFMAs lie between two barriers, so
+// the two workgroups of a CU (77 KB of LDS at R = 5) cover each other's waits.  Bound by the matrix cores.
+// Against fp32 MFMAs (32x32x2, one 16-bit-sized pipeline per CU): conv3 on 8 maps of 37 x 49 594 -> 176 us
+// (146 TFLOP/s of fp32 work, 0.88 PFLOP/s of bf16 products), conv2 of a 480 x 640 image's 8-scale pyramid
+// 624 -> 141 us; error against 64 bits 7.1e-7 -> 2.6e-7 of the 2-norm.
+// ------------------------------------------------------------------------------------------------
+template <int R>
+struct SplitCfg {
+  using Cf = ConvCfg<__bf16, R, 64, 2, 1616, 2>;
+  static constexpr int BM = 64, NT = 256, NW = 4, TM = 2, TN = 2;
+  static constexpr int TS = 3, NS = (R * R + TS - 1) / TS;  // taps per stage, stages per chunk
+  static constexpr int HALO_E = Cf::HH * Cf::RS;            // elements of one of the three halo planes
+  static constexpr int TAP_E = 3 * BM * 16;                 // elements of one tap's weights
+  static constexpr int W_OFF = (3 * HALO_E + 511) / 512 * 512;
+  static constexpr int LDS_E = W_OFF + 2 * TS * TAP_E;
+  static constexpr int HALO_V = Cf::HH * Cf::HW * 4, HALO_PER = (HALO_V + NT - 1) / NT;  // 4 channels each
+  static_assert(NW * 64 * 64 * 2 <= LDS_E, "the fp32 epilogue staging fits the stage buffers");
+  static_assert((size_t)LDS_E * 2 <= 80 * 1024, "two workgroups per CU");
+};
+
+// Keeps the compiler from moving this wave's LDS accesses across it (a wave's own LDS operations
+// execute in order).
+__device__ inline void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// f(integral_constant<I>) for I = B .. E - 1, in order.
+template <int B, int E, typename F>
+__device__ inline void static_for(F&& f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
+
+// ksplit > 1 (launches too small to fill the chip): the launch is ksplit copies of its base workgroups;
+// copy ks runs the input-channel chunks [ks nchunks / ksplit, (ks + 1) nchunks / ksplit) and writes its
+// raw sums (no bias, no ReLU) to part + ks part_slice at the output's element offsets;
+// split_reduce_kernel then adds the copies in order.
+// wsplit: per block of 64 output channels, chunk of 16 input channels and tap: [3][64][2 slots] of bf16,
+// in the order of the LDS buffer.  w: the fp32 weights [M][R R][Cg] and special: whether any of them
+// does not split.  scalar: compute with scalar FMAs only (maps whose tiles exceed 32-bit byte offsets).
+template <int R, bool MULTI>
+__global__ __launch_bounds__(256, 2) void conv_f32_kernel(
+    const float* __restrict__ in, float* __restrict__ out, const __bf16* __restrict__ wsplit,
+    const float* __restrict__ w, const uint32_t* __restrict__ special, const float* __restrict__ bias,
+    KRuns runs, int C, int Cg, int M, int Mg, int mblocks, int ksplit, int base, float* __restrict__ part,
+    int64_t part_slice, int scalar) {
+  using P = SplitCfg<R>;
+  using Cf = typename P::Cf;
+  using Op = Mfma<__bf16>;
+  using frag = typename Op::frag;
+  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  constexpr int pad = (R - 1) / 2, TM = P::TM, TN = P::TN, RR = R * R;
+  __shared__ __align__(1024) __bf16 s_mem[P::LDS_E];
+
+  // XCD-aware order, as conv_s1_direct_kernel
+  const int nb = gridDim.x, xcd = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
+  int bid = xcd * per + min(xcd, rem) + blockIdx.x / 8;
+  const int ks = bid / base;
+  bid -= ks * base;
+  const KRun& rn = runs.r[run_of<MULTI>(runs, bid)];
+  bid -= rn.first;
+  const int H = rn.H, W = rn.W, tiles_x = rn.tiles_x, tiles_y = rn.tiles_y;
+  const int mb = bid % mblocks;
+  bid /= mblocks;
+  const int tx = bid % tiles_x;
+  bid /= tiles_x;
+  const int ty = bid % tiles_y;
+  const int plane = bid / tiles_y;
+  const int mpg = Mg / P::BM;
+  const int g = mb / mpg, m0 = (mb % mpg) * P::BM;  // group, first output channel within it
+  const int oy0 = ty * Cf::TH, ox0 = tx * Cf::TW;
+  const float* src = in + rn.in_off + plane * rn.in_stride + g * Cg;
+  const int nchunks = Cg / 16;
+  const int c_lo = ks * nchunks / ksplit, c_hi = (ks + 1) * nchunks / ksplit;
+
+  const int tid = threadIdx.x, lane = tid & 63, wn = tid >> 6;
+  const int half = lane >> 5, l32 = lane & 31;
+  constexpr uint32_t OOB = 0x80000000u;
+
+  // Halo loads: 4 channels of a pixel each, at byte offsets from the tile's first halo row in the map
+  // (a tile's rows span less than 2^31 bytes, or `scalar` is set).
+  const int iy_first = max(oy0 - pad, 0);
+  const float* row0 = src + (int64_t)iy_first * W * C;
+  const int64_t span = (int64_t)(min(oy0 + Cf::TH + pad, H) - iy_first) * W * C - g * Cg;
+  const __amdgpu_buffer_rsrc_t rsrc_in = uniform_rsrc(row0, (uint32_t)(span * sizeof(float)));
+  uint32_t hoff[P::HALO_PER];
+#pragma unroll
+  for (int i = 0; i < P::HALO_PER; ++i) {
+    const int e = tid + i * P::NT, v = e & 3, p = e >> 2;
+    const int iy = oy0 - pad + p / Cf::HW, ix = ox0 - pad + p % Cf::HW;
+    const bool ok = e < P::HALO_V && iy >= 0 && iy < H && ix >= 0 && ix < W;
+    hoff[i] = ok ? (uint32_t)((((iy - iy_first) * W + ix) * C + 4 * v) * (int)sizeof(float)) : OOB;
+  }
+  u32x4_t hreg[P::HALO_PER];
+  auto load_halo = [&](int chunk) {
+#pragma unroll
+    for (int i = 0; i < P::HALO_PER; ++i)
+      hreg[i] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc_in, hoff[i], chunk * 64, 0));
+  };
+  uint32_t top = 0;  // largest |x| staged, as bits
+  auto store_halo = [&] {
+    typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int i = 0; i < P::HALO_PER; ++i) {
+      const int e = tid + i * P::NT, v = e & 3, p = e >> 2;
+      if (e < P::HALO_V) {
+        bf4 h, m, l;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t bits = hreg[i][q];
+          const Split3 sp = split3(__builtin_bit_cast(float, bits));
+          h[q] = sp.h, m[q] = sp.m, l[q] = sp.l;
+          top = max(top, bits & 0x7fffffffu);
+        }
+        __bf16* d = s_mem + Cf::halo_off(p / Cf::HW, p % Cf::HW, v >> 1) + 4 * (v & 1);
+        *(bf4*)d = h;
+        *(bf4*)(d + P::HALO_E) = m;
+        *(bf4*)(d + 2 * P::HALO_E) = l;
+      }
+    }
+  };
+  // Weights of stage s (taps 3 s ..) of a chunk: whole 1 KB pieces, dealt to the waves in turn.
+  const __bf16* wg = wsplit + (int64_t)(g * mpg + m0 / P::BM) * nchunks * RR * P::TAP_E;
+  const __amdgpu_buffer_rsrc_t rsrc_w =
+      uniform_rsrc(wg, (uint32_t)(nchunks * RR * P::TAP_E * (int)sizeof(__bf16)));
+  const int wave_s = __builtin_amdgcn_readfirstlane(wn);
+  const uint32_t lane16 = (uint32_t)lane * 16u;
+  auto load_w = [&](int buf, int chunk, auto sc) {
+    constexpr int S = decltype(sc)::value;
+    constexpr int TAPS = RR - P::TS * S < P::TS ? RR - P::TS * S : P::TS, PIECES = TAPS * P::TAP_E / 512;
+    const uint32_t from = (uint32_t)((chunk * RR + P::TS * S) * P::TAP_E) * 2u;
+#pragma unroll
+    for (int i = 0; i < (PIECES + P::NW - 1) / P::NW; ++i) {
+      const int q = wave_s + P::NW * i;
+      if (q < PIECES)
+        lds_direct16(rsrc_w, s_mem + P::W_OFF + buf * (P::TS * P::TAP_E) + q * 512, lane16, from + q * 1024u);
+    }
+  };
+
+  // Pixel layouts and skipped MFMA tiles at the map's edges as in conv_s1_direct_kernel.
+  auto gtile = [&](int t) { return t * Cf::WN + wn; };
+  const int cv = min(Cf::TW, W - ox0), rv = min(Cf::TH, H - oy0);
+  const int n_rows = (rv + 1) / 2, n_cols = (cv + 1) / 2;
+  const bool colpair = n_cols < n_rows;
+  const int n_mt = colpair ? n_cols : n_rows;
+  auto out_row = [&](int idx) { return colpair ? (idx & 15) : Cf::pix_row(idx); };
+  auto out_col = [&](int idx) { return colpair ? 2 * (idx >> 5) + ((idx >> 4) & 1) : Cf::pix_col(idx); };
+  int pix[TN];
+  int tnv = 0;
+#pragma unroll
+  for (int t = 0; t < TN; ++t) {
+    const int idx = gtile(t) * 32 + l32;
+    pix[t] = Cf::halo_off(out_row(idx), out_col(idx), half);
+    tnv += gtile(t) < n_mt ? 1 : 0;
+  }
+  tnv = __builtin_amdgcn_readfirstlane(tnv);
+
+  f32x16 big[TM][TN], small[TM][TN];  // sums of h h', and of the five small terms
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int t = 0; t < TN; ++t) big[a][t] = f32x16{}, small[a][t] = f32x16{};
+
+  auto chunks = [&](auto tnv_c) {
+    constexpr int TNV = decltype(tnv_c)::value;
+    load_halo(c_lo);
+    load_w(0, c_lo, std::integral_constant<int, 0>{});
+    store_halo();
+    wait_vmem();
+    __syncthreads();
+    int buf = 0;
+    for (int chunk = c_lo; chunk < c_hi; ++chunk) {
+      const bool next = chunk + 1 < c_hi;
+      if (next) load_halo(chunk + 1);
+      static_for<0, P::NS>([&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        if constexpr (S + 1 < P::NS)
+          load_w(buf ^ 1, chunk, std::integral_constant<int, S + 1>{});
+        else if (next)
+          load_w(buf ^ 1, chunk + 1, std::integral_constant<int, 0>{});
+        if constexpr (TNV > 0) {
+          const __bf16* ws = s_mem + P::W_OFF + buf * (P::TS * P::TAP_E);
+          static_for<P::TS * S, (P::TS * (S + 1) < RR ? P::TS * (S + 1) : RR)>([&](auto tc) {
+            constexpr int TAP = decltype(tc)::value, KY = TAP / R, KX = TAP % R;
+            frag x[3][TNV], wf[3][TM];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+#pragma unroll
+              for (int t = 0; t < TNV; ++t)
+                x[k][t] = *(const frag*)(s_mem + pix[t] + k * P::HALO_E + KY * Cf::RS + KX * Cf::PS);
+#pragma unroll
+              for (int mt = 0; mt < TM; ++mt)
+                wf[k][mt] = *(const frag*)(ws + (TAP - P::TS * S) * P::TAP_E + k * (P::BM * 16) +
+                                           Cf::w_off(0, mt * 32 + l32, half));
+            }
+            auto term = [&](int kw, int kx, f32x16 (&acc)[TM][TN]) {
+#pragma unroll
+              for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+                for (int t = 0; t < TNV; ++t) acc[mt][t] = Op::mma(wf[kw][mt], x[kx][t], acc[mt][t]);
+            };
+            term(0, 0, big);
+            term(2, 0, small);
+            term(0, 2, small);
+            term(1, 1, small);
+            term(1, 0, small);
+            term(0, 1, small);
+          });
+        }
+        wait_vmem();
+        if constexpr (S + 1 == P::NS) {
+          if (next) {
+            __syncthreads();  // every wave is done with this chunk's halo
+            store_halo();
+          }
+        }
+        __syncthreads();
+        buf ^= 1;
+      });
+    }
+  };
+  if (!scalar) switch (tnv) {
+    case 2: chunks(std::integral_constant<int, 2>{}); break;
+    case 1: chunks(std::integral_constant<int, 1>{}); break;
+    default: chunks(std::integral_constant<int, 0>{}); break;
+  }
+
+  const bool raw = ksplit > 1;  // raw sums of this copy
+  float* dst = (raw ? part + ks * part_slice : out) + rn.out_off + plane * rn.out_stride;
+  const int mw = g * Mg + m0;  // first output channel
+  if (__syncthreads_or(top >= SPLIT_LIMIT) || *special || scalar) {
+    // Some value does not split: this workgroup's outputs in fp32, one pixel per thread.
+    const int oy = oy0 + tid / 16, ox = ox0 + tid % 16;
+    if (oy >= H || ox >= W) return;
+    for (int m = 0; m < P::BM; ++m) {
+      const float* wm = w + (int64_t)(mw + m) * RR * Cg;
+      float acc = 0.f;
+      for (int c = 16 * c_lo; c < 16 * c_hi; ++c)
+        for (int t = 0; t < RR; ++t) {
+          const int iy = oy + t / R - pad, ix = ox + t % R - pad;
+          const float x = iy >= 0 && iy < H && ix >= 0 && ix < W ? src[((int64_t)iy * W + ix) * C + c] : 0.f;
+          acc = __builtin_fmaf(x, wm[t * Cg + c], acc);
+        }
+      dst[((int64_t)oy * W + ox) * M + mw + m] = raw ? acc : fmaxf(acc + bias[mw + m], 0.f);
+    }
+    return;
+  }
+
+  // Epilogue: each wave stages its 64 pixels x 64 channels (256-byte rows, 16-byte chunks swizzled by
+  // the pixel) and writes whole rows, 16 lanes per pixel.
+  float* stg = (float*)s_mem + wn * (64 * 64);
+#pragma unroll
+  for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int t = 0; t < TN; ++t) {
+        const int p = t * 32 + l32, j = 8 * mt + 2 * q + half;
+        f32x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = big[mt][t][4 * q + e] + small[mt][t][4 * q + e];
+        *(f32x4*)(stg + p * 64 + ((j ^ (p & 15)) * 4)) = r;
+      }
+  wave_lds_order();
+  const int j = lane & 15;
+  const f32x4 bv = *(const f32x4*)(bias + mw + 4 * j);
+#pragma unroll
+  for (int it = 0; it < 16; ++it) {
+    const int p = it * 4 + (lane >> 4);
+    f32x4 r = *(const f32x4*)(stg + p * 64 + ((j ^ (p & 15)) * 4));
+    const int idx = gtile(p >> 5) * 32 + (p & 31);
+    const int oy = oy0 + out_row(idx), ox = ox0 + out_col(idx);
+    if (oy < H && ox < W) {
+      float* d = dst + ((int64_t)oy * W + ox) * M + mw + 4 * j;
+      if (raw) {
+        *(f32x4*)d = r;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = fmaxf(r[e] + bv[e], 0.f);
+        __builtin_nontemporal_store(r, (f32x4*)d);
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// conv1 for fp32 storage, on bf16 matrix cores as conv_f32_kernel: three bf16 parts of each value, six
+// products.  Workgroup: 16 x 16 output pixels x 96 channels, four waves of 96 channels x 64 pixels.
+// Per input channel its 72 x 72 input halo sits in LDS as three bf16 planes and nine k-steps (12 x 12
+// taps, zero weights at 11) run over it; the weights stream through two buffers of two k-steps.  The
+// next channel's halo is loaded into registers meanwhile.  With 3 x 2 MFMA tiles per wave there is no
+// room for two accumulators each at two waves per SIMD, so one takes all terms: 162 roundings of a sum,
+// against 216 with fp32 MFMAs of two k.  Bound by the matrix cores, 10 % of it the zero taps; against
+// fp32 MFMAs, conv1 of a 480 x 640 image's 8-scale pyramid 295 -> 95 us.
+// ------------------------------------------------------------------------------------------------
+struct Split1 {
+  static constexpr int NT = 256, NW = 4, TM = 3, TN = 2, HR = 72, HS = 80;
+  static constexpr int NK = K1 / 16, TS = 2, NS = (NK + TS - 1) / TS;  // k-steps per channel and stage, stages
+  static constexpr int HALO_E = HR * HS, KSE = 3 * 96 * 16;            // elements of a plane, of a k-step
+  static constexpr int W_OFF = (3 * HALO_E + 511) / 512 * 512;
+  static constexpr int LDS_E = W_OFF + 2 * TS * KSE;
+  static constexpr int HALO_V = HR * HR / 4, HALO_PER = (HALO_V + NT - 1) / NT;
+  static_assert(NW * 32 * 96 * 2 <= LDS_E, "the fp32 epilogue staging (32 pixels per wave) fits");
+  static_assert((size_t)LDS_E * 2 <= 80 * 1024, "two workgroups per CU");
+};
+
+// wsplit: per input channel and k-step [3][96][2 slots] of bf16, in LDS order; w: [96][3][144] fp32.
+// ksplit > 1: as conv_f32_kernel's split, over the three input channels.
+template <bool MULTI>
+__global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restrict__ in, float* __restrict__ out,
+                                                           const __bf16* __restrict__ wsplit,
+                                                           const float* __restrict__ w,
+                                                           const uint32_t* __restrict__ special,
+                                                           const float* __restrict__ bias, KRuns runs, int ksplit,
+                                                           int base, float* __restrict__ part,
+                                                           int64_t part_slice) {
+  using P = Split1;
+  using Op = Mfma<__bf16>;
+  using frag = Op::frag;
+  using hfrag = Op::half_frag;
+  typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+  constexpr int TM = P::TM, TN = P::TN;
+  __shared__ __align__(1024) __bf16 s_mem[P::LDS_E];
+
+  const int nb = gridDim.x, xcd = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
+  int bid = xcd * per + min(xcd, rem) + blockIdx.x / 8;
+  const int copy = bid / base;  // split copy: input channels [3 copy / ksplit, 3 (copy + 1) / ksplit)
+  bid -= copy * base;
+  const KRun& rn = runs.r[run_of<MULTI>(runs, bid)];
+  bid -= rn.first;
+  const int H = rn.H, W = rn.W, pitch = rn.pitch, Ho = rn.Ho, Wo = rn.Wo, tiles_x = rn.tiles_x;
+  const int tx = bid % tiles_x;
+  bid /= tiles_x;
+  const int ty = bid % rn.tiles_y, plane = bid / rn.tiles_y;
+  const int oy0 = ty * 16, ox0 = tx * 16, iy0 = 4 * oy0, ix0 = 4 * ox0;
+  const float* src = in + rn.in_off + plane * rn.in_stride;
+  const int c_lo = copy * 3 / ksplit, c_hi = (copy + 1) * 3 / ksplit;
+
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int half = lane >> 5, l32 = lane & 31;
+  constexpr uint32_t OOB = 0x80000000u;
+
+  // Halo loads: four pixels of a row each, at byte offsets from the tile's first row (the rows of one
+  // channel; 16-byte loads at 4-byte alignment).  Columns from W on are replaced by zeros.
+  const int rows = min(P::HR, H - iy0);
+  uint32_t hoff[P::HALO_PER];
+#pragma unroll
+  for (int i = 0; i < P::HALO_PER; ++i) {
+    const int e = tid + i * P::NT, r = e / 18, x = ix0 + 4 * (e % 18);
+    hoff[i] = e < P::HALO_V && r < rows && x < W ? (uint32_t)((r * pitch + x) * (int)sizeof(float)) : OOB;
+  }
+  u32x4_t hreg[P::HALO_PER];
+  auto load_halo = [&](int c) {
+    const __amdgpu_buffer_rsrc_t rsrc =
+        uniform_rsrc(src + ((int64_t)c * H + iy0) * pitch, (uint32_t)((int64_t)rows * pitch * sizeof(float)));
+#pragma unroll
+    for (int i = 0; i < P::HALO_PER; ++i)
+      hreg[i] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, hoff[i], 0, 0));
+  };
+  uint32_t top = 0;  // largest |x| staged, as bits
+  auto store_halo = [&] {
+    typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int i = 0; i < P::HALO_PER; ++i) {
+      const int e = tid + i * P::NT, r = e / 18, xc = 4 * (e % 18);
+      if (e < P::HALO_V) {
+        bf4 h, m, l;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          uint32_t bits = hreg[i][q];
+          if (ix0 + xc + q >= W) bits = 0u;
+          const Split3 sp = split3(__builtin_bit_cast(float, bits));
+          h[q] = sp.h, m[q] = sp.m, l[q] = sp.l;
+          top = max(top, bits & 0x7fffffffu);
+        }
+        __bf16* d = s_mem + r * P::HS + xc;
+        *(bf4*)d = h;
+        *(bf4*)(d + P::HALO_E) = m;
+        *(bf4*)(d + 2 * P::HALO_E) = l;
+      }
+    }
+  };
+  const __amdgpu_buffer_rsrc_t rsrc_w = uniform_rsrc(wsplit, (uint32_t)(3 * P::NK * P::KSE * (int)sizeof(__bf16)));
+  const uint32_t lane16 = (uint32_t)lane * 16u;
+  auto load_w = [&](int buf, int c, auto sc) {  // stage sc of channel c: k-steps TS sc ..
+    constexpr int S = decltype(sc)::value;
+    constexpr int STEPS = P::NK - P::TS * S < P::TS ? P::NK - P::TS * S : P::TS, PIECES = STEPS * P::KSE / 512;
+    const uint32_t from = (uint32_t)((c * P::NK + P::TS * S) * P::KSE) * 2u;
+#pragma unroll
+    for (int i = 0; i < (PIECES + P::NW - 1) / P::NW; ++i) {
+      const int q = wv + P::NW * i;
+      if (q < PIECES)
+        lds_direct16(rsrc_w, s_mem + P::W_OFF + buf * (P::TS * P::KSE) + q * 512, lane16, from + q * 1024u);
+    }
+  };
+
+  // MFMA pixel tile t of wave wv: tile rows 2 (4 t + wv) and the next, 16 columns each
+  auto gtile = [&](int t) { return t * P::NW + wv; };
+  int lpix[TN];
+  int tnv = 0;
+#pragma unroll
+  for (int t = 0; t < TN; ++t) {
+    const int idx = gtile(t) * 32 + l32;
+    lpix[t] = (4 * (idx / 16) + 2 * half) * P::HS + 4 * (idx % 16);
+    tnv += 2 * gtile(t) < Ho - oy0 ? 1 : 0;
+  }
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int t = 0; t < TN; ++t) acc[a][t] = f32x16{};
+
+  auto channels = [&](auto tnv_c) {
+    constexpr int TNV = decltype(tnv_c)::value;
+    load_halo(c_lo);
+    load_w(0, c_lo, std::integral_constant<int, 0>{});
+    store_halo();
+    wait_vmem();
+    __syncthreads();
+    int buf = 0;
+    for (int c = c_lo; c < c_hi; ++c) {
+      const bool next = c + 1 < c_hi;
+      if (next) load_halo(c + 1);
+      static_for<0, P::NS>([&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        if constexpr (S + 1 < P::NS)
+          load_w(buf ^ 1, c, std::integral_constant<int, S + 1>{});
+        else if (next)
+          load_w(buf ^ 1, c + 1, std::integral_constant<int, 0>{});
+        if constexpr (TNV > 0) {
+          const __bf16* ws = s_mem + P::W_OFF + buf * (P::TS * P::KSE);
+          static_for<P::TS * S, (P::TS * (S + 1) < P::NK ? P::TS * (S + 1) : P::NK)>([&](auto jc) {
+            constexpr int J = decltype(jc)::value, O = 4 * (J / 3) * P::HS + 4 * (J % 3);
+            frag x[3][TNV], wf[3][TM];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+#pragma unroll
+              for (int t = 0; t < TNV; ++t) {
+                const __bf16* q = s_mem + lpix[t] + k * P::HALO_E + O;
+                const hfrag lo = *(const hfrag*)q, hi = *(const hfrag*)(q + P::HS);
+                x[k][t] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+              }
+#pragma unroll
+              for (int mt = 0; mt < TM; ++mt)
+                wf[k][mt] = *(const frag*)(ws + (J - P::TS * S) * P::KSE + k * (96 * 16) + (mt * 32 + l32) * 16 +
+                                           (half ^ ((l32 >> 4) & 1)) * 8);
+            }
+            auto term = [&](int kw, int kx) {
+#pragma unroll
+              for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+                for (int t = 0; t < TNV; ++t) acc[mt][t] = Op::mma(wf[kw][mt], x[kx][t], acc[mt][t]);
+            };
+            term(2, 0);
+            term(0, 2);
+            term(1, 1);
+            term(1, 0);
+            term(0, 1);
+            term(0, 0);
+          });
+        }
+        wait_vmem();
+        if constexpr (S + 1 == P::NS) {
+          if (next) {
+            __syncthreads();  // every wave is done with this channel's halo
+            store_halo();
+          }
+        }
+        __syncthreads();
+        buf ^= 1;
+      });
+    }
+  };
+  switch (tnv) {
+    case 2: channels(std::integral_constant<int, 2>{}); break;
+    case 1: channels(std::integral_constant<int, 1>{}); break;
+    default: channels(std::integral_constant<int, 0>{}); break;
+  }
+
+  const bool raw = ksplit > 1;
+  float* dst = (raw ? part + copy * part_slice : out) + rn.out_off + plane * rn.out_stride;
+  if (__syncthreads_or(top >= SPLIT_LIMIT) || *special) {
+    // Some value does not split: this workgroup's outputs in fp32, one pixel per thread.
+    const int oy = oy0 + tid / 16, ox = ox0 + tid % 16;
+    if (oy >= Ho || ox >= Wo) return;
+    for (int m = 0; m < 96; ++m) {
+      float a = 0.f;
+      for (int c = c_lo; c < c_hi; ++c)
+        for (int k = 0; k < K1; ++k) {
+          const int ky = conv1_ky(k), kx = conv1_kx(k);
+          if (ky < 11 && kx < 11)
+            a = __builtin_fmaf(src[((int64_t)c * H + 4 * oy + ky) * pitch + 4 * ox + kx], w[(m * 3 + c) * K1 + k], a);
+        }
+      dst[((int64_t)oy * Wo + ox) * 96 + m] = raw ? a : fmaxf(a + bias[m], 0.f);
+    }
+    return;
+  }
+
+  // Epilogue: per MFMA pixel tile each wave stages 32 pixels x 96 channels (384-byte rows, 16-byte chunks
+  // swizzled by the pixel) and writes whole rows, 24 lanes per pixel.
+  float* stg = (float*)s_mem + wv * (32 * 96);
+#pragma unroll
+  for (int t = 0; t < TN; ++t) {
+    wave_lds_order();
+#pragma unroll
+    for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int j = 8 * mt + 2 * q + half;
+        f32x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = acc[mt][t][4 * q + e];
+        *(f32x4*)(stg + l32 * 96 + ((j ^ ((l32 >> 2) & 7)) * 4)) = r;
+      }
+    wave_lds_order();
+#pragma unroll
+    for (int it = 0; it < 12; ++it) {
+      const int u = it * 64 + lane, p = u / 24, j = u % 24;
+      f32x4 r = *(const f32x4*)(stg + p * 96 + ((j ^ ((p >> 2) & 7)) * 4));
+      const int idx = gtile(t) * 32 + p, oy = oy0 + idx / 16, ox = ox0 + idx % 16;
+      if (oy < Ho && ox < Wo) {
+        float* d = dst + ((int64_t)oy * Wo + ox) * 96 + 4 * j;
+        if (raw) {
+          *(f32x4*)d = r;
+        } else {
+          const f32x4 bv = *(const f32x4*)(bias + 4 * j);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) r[e] = fmaxf(r[e] + bv[e], 0.f);
+          __builtin_nontemporal_store(r, (f32x4*)d);
+        }
+      }
+    }
+  }
+}
+
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int OUT_CPOL = 2;  // cache policy of conv1's output stores: non-temporal
 // conv1's MFMA pixel tiles per wave (Conv1R): 2, chosen by timing on the 96-plane batch (4, one wave per
@@ -1123,19 +1339,6 @@ static_assert(Conv1R<2>::uchan(4 * 8) == 0 && Conv1R<2>::uchan(4 * 8 + 1) == 1 &
 static_assert(Conv1R<2>::SPX * Conv1R<2>::SROW <= Conv1R<2>::HALO_E, "epilogue staging fits a halo buffer");
 static_assert((size_t)Conv1R<2>::LDS_E * 2 <= 160 * 1024, "one workgroup's LDS fits the CU");
 static_assert((size_t)Conv1R<4>::LDS_E * 2 <= 160 * 1024, "one workgroup's LDS fits the CU");
-
-// Keeps the compiler from moving this wave's LDS accesses across it (a wave's own LDS operations
-// execute in order).
-__device__ inline void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
-// f(integral_constant<I>) for I = B .. E - 1, in order.
-template <int B, int E, typename F>
-__device__ inline void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
 
 template <typename T, int PT, bool MULTI>
 __global__ __launch_bounds__(64 * Conv1R<PT>::NWV, 1) void conv1_resident_kernel(
@@ -1367,20 +1570,21 @@ __global__ __launch_bounds__(64 * Conv1R<PT>::NWV, 1) void conv1_resident_kernel
   }
 }
 
-// Copies an fp32 launch of `blocks` workgroups splits its input channels over (at most max_copies):
-// the ks minimising rounds(ks) / ks + 0.15 [ks > 1] + 0.02 ks blocks / CUs, rounds(ks) =
-// ceil(ks blocks / CUs) (one fp32 workgroup per CU at a time): the launch's rounds of shorter
-// workgroups, plus the reduction and the partial sums' traffic, which grows with the copies and the
-// launch's output (fitted to timed launches of the 227 x 227 and the 8-scale 480 x 640 pyramids).
-// Launches of at least one workgroup per CU do not split: a lone workgroup's whole K loop sets a
-// small launch's time, not a large one's.
+// Copies an fp32 launch of `blocks` workgroups splits its input channels over (at most max_copies): the ks
+// minimising rounds(ks) / ks + 0.15 [ks > 1] + 0.02 ks blocks / slots, rounds(ks) = ceil(ks blocks / slots)
+// with two workgroups resident per CU: the launch's rounds of shorter workgroups, plus the reduction
+// and the partial sums' traffic, which grows with the copies and the launch's output.  Launches of at
+// least one round do not split: a lone workgroup's whole K loop sets a small launch's time, not a large
+// one's.  Timed at 1, 2, 3, 4, 6, 8, 12 and 16 copies: conv3 of two 13 x 13 and 9 x 9 maps (12
+// workgroups) takes 92 us unsplit, 28 at 6, 23 at 16 (chosen: 16); conv4 of the 480 x 640 pyramid's eight
+// maps (378 workgroups) 110 us unsplit, 100 at 4 (chosen), 134 at 8.
 int split_copies(int64_t blocks, int max_copies) {
-  const int64_t cus = device_cu_count();
+  const int64_t slots = 2LL * device_cu_count();
   int ks = 1;
-  if (blocks < cus) {
+  if (blocks < slots) {
     double best = 1.0;
     for (int k = 2; k <= max_copies; ++k) {
-      const double cost = (double)((k * blocks + cus - 1) / cus) / k + 0.15 + 0.02 * k * (double)blocks / cus;
+      const double cost = (double)((k * blocks + slots - 1) / slots) / k + 0.15 + 0.02 * k * (double)blocks / slots;
       if (cost < best) best = cost, ks = k;
     }
   }
@@ -1394,12 +1598,62 @@ int64_t split_span(const MapRun* runs, int n_runs) {
   return (span + 63) / 64 * 64;
 }
 
-// part / part_bytes: workspace for the partial sums of a split fp32 launch (may be NULL: no split);
-// part_need non-NULL: only report the bytes this launch would use there (0 without a split).
+// Stride-1 layers, fp32 storage.  part / part_bytes: workspace for the partial sums of a split launch (may
+// be NULL: no split); part_need non-NULL: only report the bytes this launch would use there (0 without
+// a split).
+template <int R>
+int run_conv_f32(const float* in, float* out, const float* wp, const __bf16* wsplit, const uint32_t* special,
+                 const float* bias, const MapRun* runs, int n_runs, int C, int G, int M, float* part,
+                 size_t part_bytes, size_t* part_need, hipStream_t s) {
+  using P = SplitCfg<R>;
+  using Cf = typename P::Cf;
+  const int Cg = C / G, Mg = M / G;
+  if (Mg % P::BM || Cg % 16) return (int)hipErrorInvalidValue;  // whole channel blocks and chunks per group
+  const int mblocks = M / P::BM;
+  KRuns kr;
+  const int64_t blocks = fill_kruns(runs, n_runs, kr, [&](KRun& k) {
+    k.Ho = k.H, k.Wo = k.W;
+    k.tiles_x = (k.W + Cf::TW - 1) / Cf::TW, k.tiles_y = (k.H + Cf::TH - 1) / Cf::TH;
+    return (int64_t)k.tiles_x * k.tiles_y * mblocks;
+  });
+  if (blocks <= 0) return (int)hipErrorInvalidValue;
+  // a tile's halo rows are addressed with 32-bit byte offsets (maps up to 77,000 columns wide)
+  int scalar = 0;
+  for (int i = 0; i < n_runs; ++i)
+    if ((int64_t)Cf::HH * runs[i].W * C * (int64_t)sizeof(float) >= 0x7fffffffLL) scalar = 1;
+  int ks = split_copies(blocks, Cg / 16);
+  const int64_t span = split_span(runs, n_runs);  // elements of one partial copy
+  const size_t need = ks > 1 ? (size_t)ks * (size_t)span * sizeof(float) : 0;
+  if (part_need) {
+    *part_need = need;
+    return 0;
+  }
+  if (ks > 1 && (!part || part_bytes < need)) ks = 1;
+  if (blocks * ks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
+#define DN_F32_ARGS in, out, wsplit, wp, special, bias, kr, C, Cg, M, Mg, mblocks, ks, (int)blocks, part, span, \
+                    scalar
+  if (n_runs == 1)
+    conv_f32_kernel<R, false><<<(unsigned)(blocks * ks), P::NT, 0, s>>>(DN_F32_ARGS);
+  else
+    conv_f32_kernel<R, true><<<(unsigned)(blocks * ks), P::NT, 0, s>>>(DN_F32_ARGS);
+#undef DN_F32_ARGS
+  if (ks > 1) {
+    KRuns rr;
+    const int64_t rb = fill_kruns(runs, n_runs, rr, [&](KRun& k) {
+      k.Ho = k.H, k.Wo = k.W;
+      k.tiles_x = (int)(((int64_t)k.H * k.W * M / 4 + 255) / 256), k.tiles_y = 1;
+      return (int64_t)k.tiles_x;
+    });
+    if (rb <= 0) return (int)hipErrorInvalidValue;
+    split_reduce_kernel<<<(unsigned)rb, 256, 0, s>>>(part, span, ks, bias, out, rr, M);
+  }
+  return (int)hipGetLastError();
+}
+
+// Stride-1 layers, 16-bit storage.
 template <typename T, int R, int BM, int TM, int OCC, int TS, int BMP = BM, int TN = 4>
-int run_conv_s1(const T* in, T* out, const T* wp, const T* wstage, const float* bias, const MapRun* runs,
-                int n_runs, int C, int G, int M, float* part, size_t part_bytes, size_t* part_need,
-                hipStream_t s) {
+int run_conv_s1(const T* in, T* out, const T* wstage, const float* bias, const MapRun* runs, int n_runs, int C,
+                int G, int M, hipStream_t s) {
   using Cf = ConvCfg<T, R, BM, TM, TS, TN>;
   const int Cg = C / G, Mg = M / G;
   if (Mg % BM) return (int)hipErrorInvalidValue;  // whole channel blocks per group
@@ -1411,51 +1665,16 @@ int run_conv_s1(const T* in, T* out, const T* wp, const T* wstage, const float* 
     return (int64_t)k.tiles_x * k.tiles_y * mblocks;
   });
   if (blocks <= 0) return (int)hipErrorInvalidValue;
-  if constexpr (Cf::F32 || (TM != 2 && TM != 3)) {
-    // fp32 launches too small to fill the chip split their input chunks over ks copies
-    int ks = 1;
-    int64_t span = 0;  // elements of one partial copy
-    if constexpr (Cf::F32) {
-      ks = split_copies(blocks, Cg / Cf::CC);
-      span = split_span(runs, n_runs);
-    }
-    const size_t need = ks > 1 ? (size_t)ks * (size_t)span * sizeof(float) : 0;
-    if (part_need) {
-      *part_need = need;
-      return 0;
-    }
-    if (ks > 1 && (!part || part_bytes < need)) ks = 1;
-    conv_s1_kernel<T, R, BM, TM, OCC, TS><<<(unsigned)(blocks * ks), Cf::NT, 0, s>>>(
-        in, out, wp, bias, kr, C, Cg, M, Mg, mblocks, ks, (int)blocks, part, span);
-    if constexpr (Cf::F32) {
-      if (ks > 1) {
-        KRuns rr;
-        const int64_t rb = fill_kruns(runs, n_runs, rr, [&](KRun& k) {
-          k.Ho = k.H, k.Wo = k.W;
-          k.tiles_x = (int)(((int64_t)k.H * k.W * M / 4 + 255) / 256), k.tiles_y = 1;
-          return (int64_t)k.tiles_x;
-        });
-        if (rb <= 0) return (int)hipErrorInvalidValue;
-        split_reduce_kernel<<<(unsigned)rb, 256, 0, s>>>(part, span, ks, bias, out, rr, M);
-      }
-    }
-  } else {
-    if (part_need) {
-      *part_need = 0;
-      return 0;
-    }
-    // buffer descriptors address one plane with 32-bit byte offsets
-    for (int i = 0; i < n_runs; ++i)
-      if ((int64_t)runs[i].H * runs[i].W * C * (int64_t)sizeof(T) >= 0x7fffffffLL)
-        return (int)hipErrorInvalidValue;
-    if (wstage == wp) return (int)hipErrorInvalidValue;  // the stage-major weight copy is required
-    if (n_runs == 1)
-      conv_s1_direct_kernel<T, R, BM, TM, OCC, TS, BMP, TN, false><<<(unsigned)blocks, Cf::NT, 0, s>>>(
-          in, out, wstage, bias, kr, C, Cg, M, Mg, mblocks);
-    else
-      conv_s1_direct_kernel<T, R, BM, TM, OCC, TS, BMP, TN, true><<<(unsigned)blocks, Cf::NT, 0, s>>>(
-          in, out, wstage, bias, kr, C, Cg, M, Mg, mblocks);
-  }
+  // buffer descriptors address one plane with 32-bit byte offsets
+  for (int i = 0; i < n_runs; ++i)
+    if ((int64_t)runs[i].H * runs[i].W * C * (int64_t)sizeof(T) >= 0x7fffffffLL)
+      return (int)hipErrorInvalidValue;
+  if (n_runs == 1)
+    conv_s1_direct_kernel<T, R, BM, TM, OCC, TS, BMP, TN, false><<<(unsigned)blocks, Cf::NT, 0, s>>>(
+        in, out, wstage, bias, kr, C, Cg, M, Mg, mblocks);
+  else
+    conv_s1_direct_kernel<T, R, BM, TM, OCC, TS, BMP, TN, true><<<(unsigned)blocks, Cf::NT, 0, s>>>(
+        in, out, wstage, bias, kr, C, Cg, M, Mg, mblocks);
   return (int)hipGetLastError();
 }
 
@@ -1538,8 +1757,14 @@ int conv_dispatch(int layer, const void* d_in, const MapRun* runs, int n_runs, c
         return 0;
       }
       if (ks > 1 && (!part || part_bytes < need)) ks = 1;
-      conv1_kernel<T><<<(unsigned)(blocks * ks), 256, 0, s>>>(in, out, wp, bias, kr, ks, (int)blocks, part,
-                                                            span);
+      const __bf16* wsplit = (const __bf16*)ws;
+      const uint32_t* special = (const uint32_t*)((const char*)d_packed + L.special_off);
+      if (n_runs == 1)
+        conv1_f32_kernel<false><<<(unsigned)(blocks * ks), 256, 0, s>>>(in, out, wsplit, wp, special, bias, kr, ks,
+                                                                         (int)blocks, part, span);
+      else
+        conv1_f32_kernel<true><<<(unsigned)(blocks * ks), 256, 0, s>>>(in, out, wsplit, wp, special, bias, kr, ks,
+                                                                        (int)blocks, part, span);
       if (ks > 1) {
         KRuns rr;
         const int64_t rb = fill_kruns(runs, n_runs, rr, [](KRun& k) {
@@ -1589,28 +1814,37 @@ int conv_dispatch(int layer, const void* d_in, const MapRun* runs, int n_runs, c
     return (int)hipGetLastError();
   }
   const int li = layer - 1;
-  constexpr bool F32 = std::is_same<T, float>::value;
-#define DN_RUN_ARGS in, out, wp, ws, bias, runs, n_runs, L_C[li], L_G[li], L_M[li], part, part_bytes, part_need, s
+  if constexpr (std::is_same<T, float>::value) {
+    const __bf16* wsplit = (const __bf16*)((const char*)d_packed + L.s_off[li]);
+    const uint32_t* special = (const uint32_t*)((const char*)d_packed + L.special_off) + li;
+#define DN_RUN_ARGS \
+  in, out, wp, wsplit, special, bias, runs, n_runs, L_C[li], L_G[li], L_M[li], part, part_bytes, part_need, s
+    return layer == 2 ? run_conv_f32<5>(DN_RUN_ARGS) : run_conv_f32<3>(DN_RUN_ARGS);
+#undef DN_RUN_ARGS
+  } else {
+    if (part_need) {
+      *part_need = 0;
+      return 0;
+    }
+#define DN_RUN_ARGS in, out, ws, bias, runs, n_runs, L_C[li], L_G[li], L_M[li], s
 #define DN_SMALL_CFG(l) 3, 64, 2, DN_SMALL_OCC, 1616, L_BM[l], DN_SMALL_TN
-  switch (layer) {
-    case 2:
-      return run_conv_s1<T, 5, DN_CONV2_CFG>(DN_RUN_ARGS);
-    case 3:
-      if (!F32 && small_launch<DN_CONV3_CFG>(runs, n_runs, L_M[li]))
-        return run_conv_s1<T, DN_SMALL_CFG(2)>(DN_RUN_ARGS);
-      return run_conv_s1<T, 3, DN_CONV3_CFG>(DN_RUN_ARGS);
-    case 4:
-      if (!F32 && small_launch<DN_CONV4_CFG>(runs, n_runs, L_M[li]))
-        return run_conv_s1<T, DN_SMALL_CFG(3)>(DN_RUN_ARGS);
-      return run_conv_s1<T, 3, DN_CONV4_CFG>(DN_RUN_ARGS);
-    case 5:
-      if (!F32 && small_launch<DN_CONV5_CFG>(runs, n_runs, L_M[li]))
-        return run_conv_s1<T, DN_SMALL_CFG(4)>(DN_RUN_ARGS);
-      return run_conv_s1<T, 3, DN_CONV5_CFG>(DN_RUN_ARGS);
-  }
+    switch (layer) {
+      case 2:
+        return run_conv_s1<T, 5, DN_CONV2_CFG>(DN_RUN_ARGS);
+      case 3:
+        if (small_launch<DN_CONV3_CFG>(runs, n_runs, L_M[li])) return run_conv_s1<T, DN_SMALL_CFG(2)>(DN_RUN_ARGS);
+        return run_conv_s1<T, 3, DN_CONV3_CFG>(DN_RUN_ARGS);
+      case 4:
+        if (small_launch<DN_CONV4_CFG>(runs, n_runs, L_M[li])) return run_conv_s1<T, DN_SMALL_CFG(3)>(DN_RUN_ARGS);
+        return run_conv_s1<T, 3, DN_CONV4_CFG>(DN_RUN_ARGS);
+      case 5:
+        if (small_launch<DN_CONV5_CFG>(runs, n_runs, L_M[li])) return run_conv_s1<T, DN_SMALL_CFG(4)>(DN_RUN_ARGS);
+        return run_conv_s1<T, 3, DN_CONV5_CFG>(DN_RUN_ARGS);
+    }
 #undef DN_SMALL_CFG
 #undef DN_RUN_ARGS
-  return (int)hipErrorInvalidValue;
+    return (int)hipErrorInvalidValue;
+  }
 }
 
 }  // namespace
@@ -1631,10 +1865,14 @@ PackedLayout packed_layout(dn_dtype dt) {
   }
   for (int l = 0; l < 5; ++l) {
     L.s_off[l] = 0;
-    if (dt == DN_F32) continue;
     L.s_off[l] = off;
-    off = align256(off + (l == 0 ? (size_t)C1_KSTEPS * 96 * 16
-                                  : (size_t)L_M[l] * (L_C[l] / L_G[l]) * L_R[l] * L_R[l]) * es);
+    const size_t n = l == 0 ? (size_t)(dt == DN_F32 ? 3 * K1 : C1_KSTEPS * 16) * 96
+                            : (size_t)L_M[l] * (L_C[l] / L_G[l]) * L_R[l] * L_R[l];
+    off = align256(off + (dt == DN_F32 ? n * 3 * 2 : n * es));
+  }
+  if (dt == DN_F32) {
+    L.special_off = off;
+    off = align256(off + 5 * sizeof(uint32_t));
   }
   L.total = off;
   return L;
@@ -1645,6 +1883,8 @@ int launch_pack_weights(const float* const* d_w, const float* const* d_b, dn_dty
   hipStream_t s = (hipStream_t)stream;
   const PackedLayout L = packed_layout(dt);
   char* base = (char*)d_packed;
+  uint32_t* special = (uint32_t*)(base + L.special_off);
+  if (dt == DN_F32) clear_words_kernel<<<1, 64, 0, s>>>(special, 5);
   for (int l = 0; l < 5; ++l) {
     void* dst = base + L.w_off[l];
     if (l == 0) {
@@ -1667,6 +1907,8 @@ int launch_pack_weights(const float* const* d_w, const float* const* d_b, dn_dty
     if (L.s_off[l] && l == 0) {
       const int n = C1_KSTEPS * 96 * 16;
       void* sd = base + L.s_off[0];
+      if (dt == DN_F32)
+        pack_split1_kernel<<<(3 * K1 * 96 + 255) / 256, 256, 0, s>>>(d_w[0], (__bf16*)sd, special);
       if (dt == DN_F16)
         pack_conv1_resident_kernel<_Float16><<<(n + 255) / 256, 256, 0, s>>>(d_w[0], (_Float16*)sd);
       if (dt == DN_BF16)
@@ -1676,6 +1918,8 @@ int launch_pack_weights(const float* const* d_w, const float* const* d_b, dn_dty
       const int64_t n = (int64_t)L_M[l] * Cg * L_R[l] * L_R[l];
       const unsigned nb = (unsigned)((n + 255) / 256);
       void* sd = base + L.s_off[l];
+      if (dt == DN_F32)
+        pack_split_kernel<<<nb, 256, 0, s>>>(d_w[l], (__bf16*)sd, special + l, Mg, Cg, L_R[l] * L_R[l], n);
       if (dt == DN_F16)
         pack_stage_kernel<_Float16><<<nb, 256, 0, s>>>(d_w[l], (_Float16*)sd, Mg, Cg, L_R[l], L_BM[l], n);
       if (dt == DN_BF16)

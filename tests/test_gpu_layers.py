@@ -248,3 +248,71 @@ def test_maxpool_channel_counts(D, dt, C, shape):
     out = D.densenet_maxpool(x.cuda(), DTS[dt]).float().cpu()
     ref = torch.nn.functional.max_pool2d(x.float().permute(0, 3, 1, 2), 3, 2, ceil_mode=True)
     assert torch.equal(out, ref.permute(0, 2, 3, 1))
+
+
+def f32_layer(D, layer, x, weights):
+    """densenet_conv_layer in fp32 and the same in fp64 with torch, both [n][Ho][Wo][M]."""
+    M, C, R, s, p, G = LAYERS[layer - 1]
+    ws = [(torch.zeros(m, c // g, r, r), torch.zeros(m)) for m, c, r, _, _, g in LAYERS]
+    ws[layer - 1] = weights
+    pk = D.densenet_pack_weights([(w.cuda(), b.cuda()) for w, b in ws], DTS["f32"])
+    n, H, W = (x.shape[0], x.shape[2], x.shape[3]) if layer == 1 else x.shape[:3]
+    out = D.densenet_conv_layer(layer, x.cuda(), n, H, W, DTS["f32"], pk).double().cpu()
+    xx = x if layer == 1 else x.permute(0, 3, 1, 2)
+    ref = torch.nn.functional.conv2d(xx.double(), weights[0].double(), weights[1].double(), s, p, 1, G)
+    return out, ref.clamp(min=0).permute(0, 2, 3, 1)
+
+
+# One pixel; tile edges; partial tiles whose maps are taller (row layout) and wider (column pairs) than
+# their remainders; rows of odd length in conv1 (16-byte loads at 4-byte alignment) and its smallest plane.
+@pytest.mark.parametrize("layer,shape", [(1, (1, 11, 11)), (1, (2, 75, 140)), (1, (1, 139, 77)), (1, (3, 27, 331)),
+                                         (2, (1, 1, 1)), (2, (2, 17, 33)), (3, (1, 2, 2)), (3, (2, 16, 16)),
+                                         (3, (1, 33, 5)), (4, (2, 5, 35)), (5, (1, 18, 40))])
+def test_f32_split_conv(D, layer, shape):
+    """fp32 layers on bf16 matrix cores: the three-part products are exact to 2^-25 of |x w| each, and
+    the sum of K terms is rounded at most 6 K / 16 + 2 times, each by half an ulp (2^-24) of a partial
+    sum no larger than S = sum |x w| + |b|: |error| <= (2^-25 + (6 K / 16 + 2) 2^-24) S."""
+    M, C, R, _, _, G = LAYERS[layer - 1]
+    n, H, W = shape
+    g = torch.Generator().manual_seed(H * 31 + W + layer)
+    w = torch.randn((M, C // G, R, R), generator=g) * 0.05
+    b = torch.randn(M, generator=g)
+    x = torch.randn((n, 3, H, W) if layer == 1 else (n, H, W, C), generator=g) * 40
+    out, ref = f32_layer(D, layer, x, (w, b))
+    _, total = f32_layer(D, layer, x.abs(), (w.abs(), b.abs()))
+    K = C // G * R * R * (144 / 121 if layer == 1 else 1)
+    bar = (2.0 ** -25 + (6 * K / 16 + 2) * 2.0 ** -24) * total
+    assert bool(((out - ref).abs() <= bar).all())
+    assert float((out - ref).norm() / ref.norm()) <= 1e-6
+
+
+@pytest.mark.parametrize("layer", [1, 2, 3])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 3.4e38])
+@pytest.mark.parametrize("where", ["input", "weight"])
+def test_f32_split_conv_values_that_do_not_split(D, layer, value, where):
+    """An infinity, a NaN or a value that rounds to a bf16 infinity reaches the outputs that its fp32
+    products reach (ReLU of a NaN is 0), and no others.  Inputs and weights are otherwise below 0.75 in
+    magnitude, so no product with 3.4e38 overflows fp32."""
+    M, C, R, s, p, G = LAYERS[layer - 1]
+    n, H, W = (1, 91, 87) if layer == 1 else (1, 19, 21)
+    g = torch.Generator().manual_seed(layer)
+    w = torch.randint(0, 2, (M, C // G, R, R), generator=g) * 0.5 + 0.25   # 0.25 or 0.75
+    w *= 1 - 2 * torch.randint(0, 2, w.shape, generator=g)
+    b = torch.zeros(M)
+    x = torch.rand((n, 3, H, W) if layer == 1 else (n, H, W, C), generator=g) * 0.5 + 0.25
+    if where == "weight":
+        w[5, 1, R // 2, R // 2] = value
+    elif layer == 1:
+        x[0, 1, 40, 40] = value
+    else:
+        x[0, 9, 10, 3] = value
+    out, ref = f32_layer(D, layer, x, (w, b))
+    ref = torch.nan_to_num(ref, nan=0.0, posinf=float("inf"))   # clamp(min=0) keeps NaN, ReLU by max does not
+    finite = torch.isfinite(ref)
+    big = ref > 1e30
+    assert torch.equal(torch.isfinite(out), finite) and torch.equal(out[~finite], ref[~finite])
+    rest = finite & ~big
+    assert float((out - ref)[rest].norm() / ref[rest].norm()) <= 1e-6
+    if bool((big & finite).any()):
+        sel = big & finite
+        assert float(((out - ref).abs() / ref)[sel].max()) <= 1e-5
