@@ -148,3 +148,22 @@ def test_conv_features_row_pitch_matches_packed_rows(D):
     # the bf16 layer bar (a one-ulp difference at the largest values is ~0.05 rms), and most equal
     assert torch.isfinite(a).all() and d.max() <= BARS["bf16"] * rms, (d.max().item(), rms.item())
     assert (d > 0).float().mean() < 0.1
+
+
+# Images too narrow for 4-byte taps and just wide enough; windows of one row block, of two uneven ones
+# and wider than one pass of the workgroup's columns; odd pitches store value by value.
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("H,W,S,pitch", [(1, 1, 5, 0), (6, 2, 33, 35), (5, 3, 32, 32), (9, 4, 64, 0), (40, 5, 65, 71),
+                                         (90, 700, 300, 512), (300, 90, 257, 0)])
+def test_warp_regions_source_rows_and_columns(D, dt, H, W, S, pitch):
+    """Rows kept from one output row to the next (upsampled, 1:1, downsampled by a little and a lot, both
+    edges clamped) and both ways of loading a row's taps."""
+    img = synth.image(H * 7 + W, H, W)
+    k = S / 1.9   # source pixels per column around the limit of the 4-byte loads
+    boxes = np.array([[0, 0, W, H], [-3, -2, W + 4, H + 5], [W / 3, H / 3, W / 3 + 0.5, H / 3 + 0.4],
+                      [0, 0, S, S], [-1, 0.5, 2 * S - 1, 2 * S + 0.5], [0.25, 0, 3 * S, 3.7 * S],
+                      [0, 0, 1.9 * S, 1.9 * S], [0, 0, 1.9 * S + 1, k], [W - 1.5, H - 1.5, W, H]], np.float32)
+    got = D.densenet_warp_regions(torch.from_numpy(img).cuda(), torch.from_numpy(boxes).cuda(), DTS[dt], S,
+                                  MEAN, pitch=pitch)
+    check_windows(got[..., :S], oracle.warp_regions(img, boxes, S, MEAN), dt)
+    assert not got[..., S:].any()
