@@ -185,153 +185,6 @@ __device__ inline typename Mfma<T>::frag lds_frag16(const T* p) {
   return *(const typename Mfma<T>::frag*)p;
 }
 
-// ------------------------------------------------------------------------------------------------
-// conv1 for 16-bit storage: persistent workgroups (one per CU).  All 96 x 432 packed weights stay in
-// LDS for the whole launch; each workgroup walks output tiles of 16 x 16 pixels, and while it
-// computes one tile the next tile's 3 x 72 x 72 input halo is already loading into registers (16-byte
-// loads of plane rows), to be written to the other LDS halo buffer after the tile's MFMAs.
-// Waves: 4 x (96 channels x 64 pixels); A = weights, B = pixels, so each lane stores 4 consecutive
-// output channels of one pixel per store.
-// ------------------------------------------------------------------------------------------------
-template <typename T>
-struct Conv1P {
-  static constexpr int TH = 16, TW = 16, HR = 72, HS = 80;
-  static constexpr int KT = 3 * K1, WS = KT + 8;
-  static constexpr int HV = 3 * HR * (HR / 8);  // 16-byte vectors per halo
-  static constexpr int HPER = (HV + 255) / 256;
-  static constexpr size_t LDS = sizeof(T) * (96 * WS + 2 * 3 * HR * HS);
-};
-
-template <typename T>
-__global__ __launch_bounds__(256) void conv1_persistent_kernel(
-    const T* __restrict__ in, T* __restrict__ out, const T* __restrict__ wp,
-    const float* __restrict__ bias, KRuns runs, int ntiles) {
-  using P = Conv1P<T>;
-  using Op = Mfma<T>;
-  typedef T vec8 __attribute__((ext_vector_type(8)));
-  typedef T out4_t __attribute__((ext_vector_type(4)));
-  __shared__ __align__(16) T s_w[96 * P::WS];
-  __shared__ __align__(16) T s_in[2][3 * P::HR * P::HS];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, l32 = lane & 31;
-  for (int e = tid; e < 96 * (P::KT / 8); e += 256) {
-    const int m = e / (P::KT / 8), v = e % (P::KT / 8);
-    *(vec8*)(s_w + m * P::WS + v * 8) = *(const vec8*)(wp + (int64_t)m * P::KT + v * 8);
-  }
-  int lpix[2];  // LDS offset of this lane's pixel (row 4 * prow, column 4 * pcol) per pixel tile
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int idx = wave * 64 + t * 32 + l32;
-    lpix[t] = 4 * (idx / P::TW) * P::HS + 4 * (idx % P::TW);
-  }
-  vec8 hreg[P::HPER];
-  auto load_halo = [&](int t) {
-    const KRun& rn = runs.r[run_of(runs, t)];
-    const int H = rn.H, W = rn.W, pitch = rn.pitch, tl = t - rn.first;
-    const bool vec_ok = (W % 8) == 0 && (pitch % 8) == 0;
-    const int tx = tl % rn.tiles_x, r = tl / rn.tiles_x, ty = r % rn.tiles_y, plane = r / rn.tiles_y;
-    const T* src = in + rn.in_off + plane * rn.in_stride;
-    const int iy0 = 4 * P::TH * ty, ix0 = 4 * P::TW * tx;
-#pragma unroll
-    for (int i = 0; i < P::HPER; ++i) {
-      const int e = tid + i * 256;
-      vec8 val = vec8{};
-      if (e < P::HV) {
-        const int c = e / (P::HR * 9), rem = e % (P::HR * 9);
-        const int iy = iy0 + rem / 9, ix = ix0 + 8 * (rem % 9);
-        if (iy < H) {
-          const T* rowp = src + ((int64_t)c * H + iy) * pitch;
-          if (vec_ok && ix + 8 <= W) {
-            val = *(const vec8*)(rowp + ix);
-          } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-              if (ix + q < W) val[q] = rowp[ix + q];
-          }
-        }
-      }
-      hreg[i] = val;
-    }
-  };
-  auto store_halo = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < P::HPER; ++i) {
-      const int e = tid + i * 256;
-      if (e < P::HV) {
-        const int c = e / (P::HR * 9), rem = e % (P::HR * 9);
-        *(vec8*)(s_in[buf] + (c * P::HR + rem / 9) * P::HS + 8 * (rem % 9)) = hreg[i];
-      }
-    }
-  };
-
-  int t = blockIdx.x;
-  if (t < ntiles) {
-    load_halo(t);
-    store_halo(0);
-  }
-  __syncthreads();
-  int buf = 0;
-  for (; t < ntiles; t += gridDim.x) {
-    const int tn = t + gridDim.x;
-    if (tn < ntiles) load_halo(tn);
-    f32x16 acc[3][2];
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) acc[a][b] = f32x16{};
-    const T* hs = s_in[buf];
-#pragma unroll 1
-    for (int c = 0; c < 3; ++c) {
-#pragma unroll
-      for (int ks = 0; ks < K1 / 16; ++ks) {
-        // k-step ks of channel c: rows ky, ky + 1 (ky = 4 (ks / 3) + 2 half), columns 4 (ks % 3) + 0..3
-        const int o0 = (c * P::HR + 4 * (ks / 3) + 2 * half) * P::HS + 4 * (ks % 3);
-        typename Op::frag x[2], w[3];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const typename Op::half_frag lo = *(const typename Op::half_frag*)(hs + lpix[b] + o0);
-          const typename Op::half_frag hi = *(const typename Op::half_frag*)(hs + lpix[b] + o0 + P::HS);
-          x[b] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        }
-#pragma unroll
-        for (int mt = 0; mt < 3; ++mt)
-          w[mt] = *(const typename Op::frag*)(s_w + (mt * 32 + l32) * P::WS + c * K1 + ks * 16 + half * 8);
-#pragma unroll
-        for (int mt = 0; mt < 3; ++mt)
-#pragma unroll
-          for (int b = 0; b < 2; ++b) acc[mt][b] = Op::mma(w[mt], x[b], acc[mt][b]);
-      }
-    }
-    if (tn < ntiles) store_halo(buf ^ 1);
-    // epilogue: bias + ReLU, 4 consecutive channels per store
-    const KRun& rn = runs.r[run_of(runs, t)];
-    const int Ho = rn.Ho, Wo = rn.Wo, tl = t - rn.first;
-    const int tx = tl % rn.tiles_x, r = tl / rn.tiles_x, ty = r % rn.tiles_y, plane = r / rn.tiles_y;
-    T* dst = out + rn.out_off + plane * rn.out_stride;
-#pragma unroll
-    for (int mt = 0; mt < 3; ++mt)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int m = mt * 32 + 8 * q + 4 * half;
-        const f32x4 bv = *(const f32x4*)(bias + m);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const int idx = wave * 64 + b * 32 + l32;
-          const int oy = ty * P::TH + idx / P::TW, ox = tx * P::TW + idx % P::TW;
-          if (oy < Ho && ox < Wo) {
-            out4_t v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = from_f32<T>(fmaxf(acc[mt][b][4 * q + e] + bv[e], 0.f));
-            *(out4_t*)(dst + ((int64_t)oy * Wo + ox) * 96 + m) = v;
-          }
-        }
-      }
-    __syncthreads();
-    buf ^= 1;
-  }
-}
-
 // Compute units of the device current at the first call (256 if the query fails), queried once;
 // the initialisation is thread-safe.
 int device_cu_count() {
@@ -1293,9 +1146,8 @@ __device__ inline void wait_vmem_upto() {
 }
 
 // ------------------------------------------------------------------------------------------------
-// conv1 for 16-bit storage with direct global->LDS loads (plane width a multiple of 8, 16-byte
-// aligned planes), weights resident, one independent pipeline per wave.  A workgroup of 8 waves (one
-// per CU, two waves per SIMD) loads all weights (75 KB) into LDS once, as 25 k-steps of 16 (the 363
+// conv1 for 16-bit storage with direct global->LDS loads (DIRECT: rows that start on 16 bytes), weights
+// resident, one independent pipeline per wave.  A workgroup of 8 waves (one per CU, two waves per SIMD) loads all weights (75 KB) into LDS once, as 25 k-steps of 16 (the 363
 // taps of an output channel as 99 units of 4 taps: see pack_conv1_resident_kernel) x 96 channels x
 // two 16-byte slots, the slots swapped for channels 16..31 of every 32-channel group, so that the 32
 // lanes of a half-wave reading one k-step's 16 bytes of 32 channels hit distinct slots modulo 512
@@ -1308,6 +1160,11 @@ __device__ inline void wait_vmem_upto() {
 // load reuses the older one.  A wave that writes out a tile, or waits for a load, stalls only
 // itself; the other wave on its SIMD keeps the MFMAs busy.  A tile's outputs leave through LDS, as
 // whole 192-byte pixel rows.
+// DIRECT = false, for rows at any alignment (pitches that are not multiples of 8, unaligned pointers,
+// planes beyond 2^31 bytes): the halo is loaded into registers, 16 bytes at 2-byte alignment, and
+// written to LDS where the direct loads are waited for, with the columns past the row's end zeroed.
+// 64 planes of 227 x 227 in fp16: 24.7 us (0.55 PFLOP/s), against 82 for a kernel of 16 x 16 tiles per
+// workgroup that loaded such rows value by value.
 // ------------------------------------------------------------------------------------------------
 // PT: 32-pixel MFMA tiles per wave (2: wave tiles of 4 x 16 pixels, 8 waves per workgroup, two per
 // SIMD; 4: 8 x 16 pixels, 4 waves, one per SIMD, 30 % fewer LDS bytes per MFMA).
@@ -1340,7 +1197,7 @@ static_assert(Conv1R<2>::SPX * Conv1R<2>::SROW <= Conv1R<2>::HALO_E, "epilogue s
 static_assert((size_t)Conv1R<2>::LDS_E * 2 <= 160 * 1024, "one workgroup's LDS fits the CU");
 static_assert((size_t)Conv1R<4>::LDS_E * 2 <= 160 * 1024, "one workgroup's LDS fits the CU");
 
-template <typename T, int PT, bool MULTI>
+template <typename T, int PT, bool MULTI, bool DIRECT>
 __global__ __launch_bounds__(64 * Conv1R<PT>::NWV, 1) void conv1_resident_kernel(
     const T* __restrict__ in, T* __restrict__ out, const T* __restrict__ wp,
     const float* __restrict__ bias, KRuns runs, int ntiles) {
@@ -1377,41 +1234,95 @@ __global__ __launch_bounds__(64 * Conv1R<PT>::NWV, 1) void conv1_resident_kernel
       if (q < P::WP) lds_direct16(rsrc_w, s_mem + q * 512, (uint32_t)(q * 1024 + lane * 16));
     }
   }
-  uint32_t chan_bytes = 0;  // bytes of one input channel of the current tile's plane
   auto hbuf = [&](int b) { return s_mem + P::HALO_OFF + (2 * wave + b) * P::HALO_E; };
-  uint32_t hoff[P::NH];
+  // The current tile's input.  DIRECT: a descriptor of its plane and byte offsets of this lane's halo
+  // slots in channel 0.  Otherwise: its plane, the tile's first row and column, and the loaded slots.
+  uint32_t chan_bytes = 0;  // bytes of one input channel of the plane
+  uint32_t hoff[DIRECT ? P::NH : 1];
   __amdgpu_buffer_rsrc_t rsrc_in;
+  const T* tsrc = in;
+  int tH = 0, tW = 0, tpitch = 0, ty0 = 0, tx0 = 0;
+  vec8_t hreg[DIRECT ? 1 : P::NH];
   // Column W of the plane is the zero-weight tap (kx = 11) of the last output column when
   // (W - 11) % 4 == 0.  With W % 8 != 0 its 16-byte slot starts inside the row and is loaded, so when
   // rows are padded (pitch > W) the padding value would enter as 0 * x; zcol is then that column's
   // position in the tile's halo (else -1) and the halo copy of it is overwritten with zeros.
   int zcol = -1;
-  auto set_tile = [&](int t) {  // input descriptor and halo slot offsets of wave tile t
+  auto set_tile = [&](int t) {  // wave tile t is the current tile
     const KRun& rn = runs.r[run_of<MULTI>(runs, t)];
     const int H = rn.H, W = rn.W, pitch = rn.pitch, tl = t - rn.first;
     const int tx = tl % rn.tiles_x, rr = tl / rn.tiles_x, ty = rr % rn.tiles_y, plane = rr / rn.tiles_y;
-    chan_bytes = (uint32_t)((int64_t)H * pitch * sizeof(T));
-    rsrc_in = uniform_rsrc(in + rn.in_off + plane * rn.in_stride, 3 * chan_bytes);
     const int iy0 = 4 * P::TH * ty, ix0 = 4 * P::TW * tx;
-    const bool zero_col_w = W % 8 != 0 && pitch > W;
-    zcol = __builtin_amdgcn_readfirstlane(zero_col_w && W >= ix0 && W < ix0 + 72 ? W - ix0 : -1);
+    if constexpr (DIRECT) {
+      chan_bytes = (uint32_t)((int64_t)H * pitch * sizeof(T));
+      rsrc_in = uniform_rsrc(in + rn.in_off + plane * rn.in_stride, 3 * chan_bytes);
+      const bool zero_col_w = W % 8 != 0 && pitch > W;
+      zcol = __builtin_amdgcn_readfirstlane(zero_col_w && W >= ix0 && W < ix0 + 72 ? W - ix0 : -1);
 #pragma unroll
-    for (int i = 0; i < P::NH; ++i) {
-      const int q = i * 64 + lane;
-      const int row = q / P::HSL, r = q % P::HSL;
-      const int iy = iy0 + row, ix = ix0 + 8 * r;
-      const bool ok = row < P::HR && r < 9 && iy < H && ix < W;
-      hoff[i] = ok ? (uint32_t)(((int64_t)iy * pitch + ix) * sizeof(T)) : OOB;
+      for (int i = 0; i < P::NH; ++i) {
+        const int q = i * 64 + lane;
+        const int row = q / P::HSL, r = q % P::HSL;
+        const int iy = iy0 + row, ix = ix0 + 8 * r;
+        const bool ok = row < P::HR && r < 9 && iy < H && ix < W;
+        hoff[i] = ok ? (uint32_t)(((int64_t)iy * pitch + ix) * sizeof(T)) : OOB;
+      }
+    } else {
+      tsrc = in + rn.in_off + plane * rn.in_stride;
+      tH = H, tW = W, tpitch = pitch, ty0 = iy0, tx0 = ix0;
     }
   };
-  auto load_halo = [&](int b, int c) {  // channel c of the current tile into buffer b
+  // load_halo: channel c of the current tile on its way to buffer b; land: it is there.
+  auto load_halo = [&](int b, int c) {
+    if constexpr (DIRECT) {
 #pragma unroll
-    for (int i = 0; i < P::NH; ++i) lds_direct16(rsrc_in, hbuf(b) + i * 512, hoff[i], c * chan_bytes);
+      for (int i = 0; i < P::NH; ++i) lds_direct16(rsrc_in, hbuf(b) + i * 512, hoff[i], c * chan_bytes);
+    } else {
+      typedef T vec8_any __attribute__((ext_vector_type(8), aligned(2)));
+      const int64_t end = (int64_t)(3 - c) * tH * tpitch;  // elements from channel c's start to the plane's end
+      const T* src = tsrc + (int64_t)c * tH * tpitch;
+#pragma unroll
+      for (int i = 0; i < P::NH; ++i) {
+        const int q = i * 64 + lane;
+        const int row = q / P::HSL, r = q % P::HSL;
+        const int iy = ty0 + row, ix = tx0 + 8 * r;
+        vec8_t v = vec8_t{};
+        if (row < P::HR && r < 9 && iy < tH && ix < tW) {
+          const int64_t at = (int64_t)iy * tpitch + ix;
+          if (at + 8 <= end) {
+            v = *(const vec8_any*)(src + at);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (ix + e < tW) v[e] = src[at + e];
+          }
+        }
+        hreg[i] = v;
+      }
+    }
   };
-  auto zero_col = [&](int b) {  // after buffer b's loads have landed
+  auto zero_col = [&](int b) {  // after buffer b's direct loads have landed
     if (zcol >= 0) {
       wave_lds_order();
       if (lane < P::HR) hbuf(b)[lane * P::HS + zcol] = from_f32<T>(0.f);
+      wave_lds_order();
+    }
+  };
+  auto land = [&](int b) {
+    if constexpr (DIRECT) {
+      wait_vmem();
+      zero_col(b);
+    } else {
+      wave_lds_order();
+#pragma unroll
+      for (int i = 0; i < P::NH; ++i) {
+        const int q = i * 64 + lane, ix = tx0 + 8 * (q % P::HSL);
+        vec8_t v = hreg[i];
+        if (tx0 + 72 > tW) {  // what follows the row in a slot that crosses its end
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = ix + e < tW ? v[e] : from_f32<T>(0.f);
+        }
+        *(vec8_t*)(hbuf(b) + q * 8) = v;
+      }
       wave_lds_order();
     }
   };
@@ -1463,7 +1374,7 @@ __global__ __launch_bounds__(64 * Conv1R<PT>::NWV, 1) void conv1_resident_kernel
   }
   wait_vmem();
   __syncthreads();  // weights and biases are in LDS; from here on each wave runs on its own
-  zero_col(0);
+  if (ntile > 0) land(0);
   // One tile per iteration, its three stages in straight-line code.  Channel 0 and channel 2 of tile
   // j sit in buffer X = j & 1, channel 1 in the other, Y; a stage's load of the next stage's channel
   // goes to the buffer its own k-steps no longer read.
@@ -1496,12 +1407,10 @@ __global__ __launch_bounds__(64 * Conv1R<PT>::NWV, 1) void conv1_resident_kernel
     };
     // stage 0: channel 0 in X; channel 1 loads into Y
     ksteps(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{}, hy, hx, [&] { load_halo((j + 1) & 1, 1); });
-    wait_vmem();
-    zero_col((j + 1) & 1);
+    land((j + 1) & 1);
     // stage 1: channel 1 in Y (k-step 8 also reads channel 0 in X); channel 2 loads into X
     ksteps(std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{}, hx, hy, [&] { load_halo(j & 1, 2); });
-    wait_vmem();
-    zero_col(j & 1);
+    land(j & 1);
     // stage 2: channel 2 in X (k-step 16 also reads channel 1 in Y); the next tile's channel 0
     // loads into Y, the next tile's X
     ksteps(std::integral_constant<int, 16>{}, std::integral_constant<int, C1_KSTEPS>{}, hy, hx, [&] {
@@ -1520,8 +1429,9 @@ __global__ __launch_bounds__(64 * Conv1R<PT>::NWV, 1) void conv1_resident_kernel
       const KRun& rn = runs.r[run_of<MULTI>(runs, t)];
       const int Ho = rn.Ho, Wo = rn.Wo, tl = t - rn.first;
       const int tx = tl % rn.tiles_x, rr = tl / rn.tiles_x, ty = rr % rn.tiles_y, plane = rr / rn.tiles_y;
+      T* dst = out + rn.out_off + plane * rn.out_stride;
       const __amdgpu_buffer_rsrc_t rsrc_out =
-          uniform_rsrc(out + rn.out_off + plane * rn.out_stride, (uint32_t)((int64_t)Ho * Wo * 96 * sizeof(T)));
+          uniform_rsrc(dst, DIRECT ? (uint32_t)((int64_t)Ho * Wo * 96 * sizeof(T)) : 0u);
 #pragma unroll
       for (int b = 0; b < PT; ++b) {
         out4_t v[3][4];
@@ -1550,10 +1460,13 @@ __global__ __launch_bounds__(64 * Conv1R<PT>::NWV, 1) void conv1_resident_kernel
             const vec8_t o = *(const vec8_t*)(hs + p * P::SROW + 8 * ch);
             const int idx = b * 32 + 16 * ph + p;
             const int oy = ty * P::TH + idx / P::TW, ox = tx * P::TW + idx % P::TW;
-            const uint32_t off = oy < Ho && ox < Wo
-                                     ? (uint32_t)((((int64_t)oy * Wo + ox) * 96 + 8 * ch) * sizeof(T))
-                                     : OOB;
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rsrc_out, off, 0, OUT_CPOL);
+            const int64_t at = ((int64_t)oy * Wo + ox) * 96 + 8 * ch;
+            if constexpr (DIRECT) {
+              const uint32_t off = oy < Ho && ox < Wo ? (uint32_t)(at * sizeof(T)) : OOB;
+              __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rsrc_out, off, 0, OUT_CPOL);
+            } else if (oy < Ho && ox < Wo) {
+              *(vec8_t*)(dst + at) = o;
+            }
           }
         }
       }
@@ -1564,9 +1477,14 @@ __global__ __launch_bounds__(64 * Conv1R<PT>::NWV, 1) void conv1_resident_kernel
         for (int b = 0; b < PT; ++b) acc[a][b] = f32x16{};
       // Vector-memory operations retire in issue order: once no more than the epilogue's stores
       // are outstanding, the next tile's halo loads (issued before them) have landed in LDS.
-      wait_vmem_upto<P::EPI_STORES>();
+      if constexpr (DIRECT) wait_vmem_upto<P::EPI_STORES>();
     }
-    zero_col((j + 1) & 1);
+    if (j + 1 < ntile) {
+      if constexpr (DIRECT)
+        zero_col((j + 1) & 1);
+      else
+        land((j + 1) & 1);
+    }
   }
 }
 
@@ -1787,29 +1705,23 @@ int conv_dispatch(int layer, const void* d_in, const MapRun* runs, int n_runs, c
                  3 * r.H * pitch * (int64_t)sizeof(T) < 0x7fffffffLL &&
                  Ho * Wo * 96 * (int64_t)sizeof(T) < 0x7fffffffLL;
       }
-      if (direct) {
-        if (ws == wp) return (int)hipErrorInvalidValue;  // the stage-major weight copy is required
-        // wave tiles of 4 x 16 output pixels, 8 workers per workgroup, one workgroup per CU
-        using R1 = Conv1R<DN_CONV1_PT>;
-        const int64_t wtiles = fill_kruns(runs, n_runs, kr, [](KRun& k) {
-          k.Ho = (k.H - 11) / 4 + 1, k.Wo = (k.W - 11) / 4 + 1;
-          k.tiles_x = (k.Wo + R1::TW - 1) / R1::TW, k.tiles_y = (k.Ho + R1::TH - 1) / R1::TH;
-          return (int64_t)k.tiles_x * k.tiles_y;
-        });
-        if (wtiles <= 0) return (int)hipErrorInvalidValue;
-        const int grid = (int)std::min<int64_t>((wtiles + R1::NWV - 1) / R1::NWV, device_cu_count());
-        if (n_runs == 1)
-          conv1_resident_kernel<T, DN_CONV1_PT, false><<<grid, 64 * R1::NWV, 0, s>>>(in, out, ws, bias, kr,
-                                                                                    (int)wtiles);
-        else
-          conv1_resident_kernel<T, DN_CONV1_PT, true><<<grid, 64 * R1::NWV, 0, s>>>(in, out, ws, bias, kr,
-                                                                                   (int)wtiles);
-      } else {
-        const int64_t blocks = fill_kruns(runs, n_runs, kr, tiles16);
-        if (blocks <= 0) return (int)hipErrorInvalidValue;
-        const int grid = (int)std::min<int64_t>(blocks, device_cu_count());
-        conv1_persistent_kernel<T><<<grid, 256, 0, s>>>(in, out, wp, bias, kr, (int)blocks);
-      }
+      // wave tiles of 4 x 16 output pixels, 8 workers per workgroup, one workgroup per CU
+      using R1 = Conv1R<DN_CONV1_PT>;
+      const int64_t wtiles = fill_kruns(runs, n_runs, kr, [](KRun& k) {
+        k.Ho = (k.H - 11) / 4 + 1, k.Wo = (k.W - 11) / 4 + 1;
+        k.tiles_x = (k.Wo + R1::TW - 1) / R1::TW, k.tiles_y = (k.Ho + R1::TH - 1) / R1::TH;
+        return (int64_t)k.tiles_x * k.tiles_y;
+      });
+      if (wtiles <= 0) return (int)hipErrorInvalidValue;
+      const int grid = (int)std::min<int64_t>((wtiles + R1::NWV - 1) / R1::NWV, device_cu_count());
+      auto go = [&](auto multi, auto dir) {
+        conv1_resident_kernel<T, DN_CONV1_PT, decltype(multi)::value, decltype(dir)::value>
+            <<<grid, 64 * R1::NWV, 0, s>>>(in, out, ws, bias, kr, (int)wtiles);
+      };
+      if (direct)
+        n_runs == 1 ? go(std::false_type{}, std::true_type{}) : go(std::true_type{}, std::true_type{});
+      else
+        n_runs == 1 ? go(std::false_type{}, std::false_type{}) : go(std::true_type{}, std::false_type{});
     }
     return (int)hipGetLastError();
   }

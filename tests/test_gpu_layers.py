@@ -316,3 +316,27 @@ def test_f32_split_conv_values_that_do_not_split(D, layer, value, where):
     if bool((big & finite).any()):
         sel = big & finite
         assert float(((out - ref).abs() / ref)[sel].max()) <= 1e-5
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+# the smallest plane; a last row whose 16-byte slot would pass the plane's end; several tiles per row
+# and column; more wave tiles than workers (256 CUs x 8) so that a worker takes several; rows on 16 bytes
+# from an unaligned pointer.
+@pytest.mark.parametrize("n,H,W,shift", [(3, 11, 11, 0), (1, 13, 17, 1), (2, 67, 139, 0), (40, 131, 227, 1),
+                                         (2, 40, 64, 3)])
+def test_conv1_rows_at_any_alignment(D, dt, n, H, W, shift):
+    """Bit-identical to the same planes with rows of 16-byte multiples (the direct loads): the padded
+    planes' extra output columns are cut off.  What surrounds the planes in memory is NaN."""
+    g = torch.Generator().manual_seed(W)
+    x = (torch.randn((n, 3, H, W), generator=g) * 50).to(TORCH_DT[dt])
+    wide = -(-W // 8) * 8
+    aligned = torch.zeros((n, 3, H, wide), dtype=x.dtype)
+    aligned[..., :W] = x
+    flat = torch.full((x.numel() + 64,), float("nan"), dtype=x.dtype)
+    flat[shift:shift + x.numel()] = x.reshape(-1)
+    flat = flat.cuda()
+    view = flat[shift:shift + x.numel()].view(n, 3, H, W)
+    out = D.densenet_conv_layer(1, view, n, H, W, DTS[dt], packed(D, dt))
+    ref = D.densenet_conv_layer(1, aligned.cuda(), n, H, wide, DTS[dt], packed(D, dt))[:, :, :(W - 11) // 4 + 1]
+    assert torch.isfinite(out.float()).all()
+    assert torch.equal(out.view(torch.int16), ref.contiguous().view(torch.int16))
