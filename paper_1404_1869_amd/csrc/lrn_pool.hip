@@ -46,7 +46,7 @@ constexpr int VECB = 16;  // bytes per channel vector
 #ifndef DN_LRN96_WPE
 #define DN_LRN96_WPE 3
 #endif
-// The tile kernel's configuration at C = 96 for 16-bit storage (channels per thread, output tile rows
+// The tile kernel's configuration at C = 96 (channels per thread, output tile rows
 // and columns, waves per SIMD), chosen by timing on the 96-plane batch: a whole pixel per thread.
 // Strip kernel configuration for C = 256 and 16-bit storage: channels per thread, pooled columns and
 // rows per workgroup, waves per SIMD (the LDS ring admits 4 workgroups per CU).  Chosen by timing on
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void lrn_pool_tile_kernel(const T* __restrict_
   }
 }
 
-// LRN (window n = 5) of CPT consecutive channels c0 .. c0 + CPT - 1 of one pixel: v holds them, lv
+// LRN (window n = 5, 16-bit storage) of CPT consecutive channels c0 .. c0 + CPT - 1 of one pixel: v holds them, lv
 // the vector just below c0 and rv the vector just above (zero beyond the channel range, which equals
 // clipping the window).  The results go to d in the storage type.
 template <typename T, int CPT>
@@ -187,42 +187,22 @@ __device__ inline void lrn_channels(const typename Vec<T>::type* v, const typena
   xs[CPT + 1] = to_f32(rv[0]);
 #pragma unroll
   for (int c = 0; c < CPT; ++c) xs[1 + c] = to_f32(v[c / N][c % N]);
-  if constexpr (sizeof(T) == 2) {
-    // Pair sums P_j = x_2j^2 + x_2j+1^2 (j = -1 .. CPT / 2, counting the neighbours' pairs), their
-    // neighbour sums Q_j = P_j + P_j+1, then window(2 i) = Q_i-1 + x_2i+2^2 and window(2 i + 1) =
-    // Q_i + x_2i-1^2: two and a half operations per channel.
-    constexpr int NP = CPT / 2;
-    float pp[NP + 2];  // pp[1 + j] = P_j
-    {
-      const float a = to_f32(lv[N - 2]), b = to_f32(rv[1]);
-      pp[0] = __builtin_fmaf(a, a, xs[0] * xs[0]);
-      pp[NP + 1] = __builtin_fmaf(b, b, xs[CPT + 1] * xs[CPT + 1]);
-    }
+  // Pair sums P_j = x_2j^2 + x_2j+1^2 (j = -1 .. CPT / 2, counting the neighbours' pairs), their
+  // neighbour sums Q_j = P_j + P_j+1, then window(2 i) = Q_i-1 + x_2i+2^2 and window(2 i + 1) =
+  // Q_i + x_2i-1^2: two and a half operations per channel.
+  constexpr int NP = CPT / 2;
+  float pp[NP + 2];  // pp[1 + j] = P_j
+  {
+    const float a = to_f32(lv[N - 2]), b = to_f32(rv[1]);
+    pp[0] = __builtin_fmaf(a, a, xs[0] * xs[0]);
+    pp[NP + 1] = __builtin_fmaf(b, b, xs[CPT + 1] * xs[CPT + 1]);
+  }
 #pragma unroll
-    for (int j = 0; j < NP; ++j) pp[1 + j] = __builtin_fmaf(xs[1 + 2 * j], xs[1 + 2 * j], xs[2 + 2 * j] * xs[2 + 2 * j]);
+  for (int j = 0; j < NP; ++j) pp[1 + j] = __builtin_fmaf(xs[1 + 2 * j], xs[1 + 2 * j], xs[2 + 2 * j] * xs[2 + 2 * j]);
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      win[2 * i] = __builtin_fmaf(xs[2 * i + 3], xs[2 * i + 3], pp[i] + pp[i + 1]);
-      win[2 * i + 1] = __builtin_fmaf(xs[2 * i], xs[2 * i], pp[i + 1] + pp[i + 2]);
-    }
-  } else {
-    // sq[2 + i] = a_i^2, pr[i] = sq[i] + sq[i + 1]: window(c) = pr[c] + pr[c + 2] + sq[c + 4]
-    float sq[CPT + 4], pr[CPT + 3];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const float a = to_f32(lv[N - 2 + i]), b = to_f32(rv[i]);
-      sq[i] = a * a;
-      sq[CPT + 2 + i] = b * b;
-    }
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const float a = to_f32(v[i / N][i % N]);
-      sq[2 + i] = a * a;
-    }
-#pragma unroll
-    for (int i = 0; i < CPT + 3; ++i) pr[i] = sq[i] + sq[i + 1];
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) win[c] = pr[c] + pr[c + 2] + sq[c + 4];
+  for (int i = 0; i < NP; ++i) {
+    win[2 * i] = __builtin_fmaf(xs[2 * i + 3], xs[2 * i + 3], pp[i] + pp[i + 1]);
+    win[2 * i + 1] = __builtin_fmaf(xs[2 * i], xs[2 * i], pp[i + 1] + pp[i + 2]);
   }
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
@@ -236,14 +216,14 @@ __device__ inline void lrn_channels(const typename Vec<T>::type* v, const typena
   }
 }
 
-// LRN then pool for C = CPT * TPP channels (96 = 96 x 1; 256 = 64 x 4 at 16-bit storage, 128 x 2 at
-// fp32) with the default window n = 5: every thread owns CPT consecutive channels of one input pixel.  It issues all of their
+// LRN then pool for C = CPT * TPP channels (96 = 96 x 1, 256 = 64 x 4), 16-bit storage and the default
+// window n = 5: every thread owns CPT consecutive channels of one input pixel.  It issues all of their
 // 16-byte loads at once (plus one neighbouring vector on each inner side when a pixel is split over
 // several threads), forms the five-channel sums of squares from pair sums, and stores the LRN result
 // to LDS.  Pixels of the tile outside the map are stored as
 // -inf, so every pooled output then takes the max over its full 3 x 3 window from LDS, unrolled, with
 // no clipping tests.  Channel count and tile shape are compile-time constants, so no index
-// arithmetic needs a division.  With 16-bit storage, a tile whose LRN values are all >= +0 (the usual
+// arithmetic needs a division.  A tile whose LRN values are all >= +0 (the usual
 // case after ReLU) takes its maxima on the raw 16-bit patterns, two per instruction (for such values,
 // and the -inf fill, signed-integer order is the float order); any other tile takes them in fp32.
 // The tile's sign is read from the inputs' sign bits (LRN keeps the sign; -0 counts as negative).
@@ -256,6 +236,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
   constexpr int NV = CPT / N, TPP = C / CPT, G = C / N, CS = C + N;
   constexpr int IW = 2 * TPW + 1, NP = (2 * TPH + 1) * IW;
   static_assert(CPT % N == 0 && C % CPT == 0 && N >= 2, "channel split must be whole vectors");
+  static_assert(sizeof(T) == 2, "16-bit storage");
   static_assert(NP * TPP <= 256, "one thread per (pixel, part)");
   typedef typename Vec<T>::type vec_t;
   __shared__ __align__(16) T s[NP * CS];
@@ -286,17 +267,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
       for (int i = 0; i < NV; ++i) v[i] = *(const vec_t*)(px + i * N);
       if (TPP > 1 && part > 0) lv = *(const vec_t*)(px - N);
       if (TPP > 1 && part + 1 < TPP) rv = *(const vec_t*)(px + CPT);
-      if constexpr (sizeof(T) == 2) {
-        typedef uint32_t uvec_t __attribute__((ext_vector_type(N / 2)));
-        uint32_t bits = 0;
+      typedef uint32_t uvec_t __attribute__((ext_vector_type(N / 2)));
+      uint32_t bits = 0;
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          const uvec_t u = __builtin_bit_cast(uvec_t, v[i]);
+      for (int i = 0; i < NV; ++i) {
+        const uvec_t u = __builtin_bit_cast(uvec_t, v[i]);
 #pragma unroll
-          for (int j = 0; j < N / 2; ++j) bits |= u[j];
-        }
-        neg = (bits & 0x80008000u) != 0;
+        for (int j = 0; j < N / 2; ++j) bits |= u[j];
       }
+      neg = (bits & 0x80008000u) != 0;
       lrn_channels<T, CPT>(v, lv, rv, d, alpha_n, beta, k);
     } else {
       vec_t f;
@@ -308,25 +287,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
   }
   const bool any_neg = __syncthreads_or(neg);
 
-  if constexpr (sizeof(T) == 2) {
-    if (!any_neg) {
-      typedef short svec_t __attribute__((ext_vector_type(N)));
-      for (int e = threadIdx.x; e < TPH * TPW * G; e += 256) {
-        const int g = e % G, q = e / G;
-        const int qy = q / TPW, qx = q % TPW;
-        const int oy = oy0 + qy, ox = ox0 + qx;
-        if (oy >= Ho || ox >= Wo) continue;
-        const T* b = s + ((2 * qy) * IW + 2 * qx) * CS + g * N;
-        svec_t m = *(const svec_t*)b;
+  if (!any_neg) {
+    typedef short svec_t __attribute__((ext_vector_type(N)));
+    for (int e = threadIdx.x; e < TPH * TPW * G; e += 256) {
+      const int g = e % G, q = e / G;
+      const int qy = q / TPW, qx = q % TPW;
+      const int oy = oy0 + qy, ox = ox0 + qx;
+      if (oy >= Ho || ox >= Wo) continue;
+      const T* b = s + ((2 * qy) * IW + 2 * qx) * CS + g * N;
+      svec_t m = *(const svec_t*)b;
 #pragma unroll
-        for (int wy = 0; wy < 3; ++wy)
+      for (int wy = 0; wy < 3; ++wy)
 #pragma unroll
-          for (int wx = 0; wx < 3; ++wx)
-            if (wy || wx) m = __builtin_elementwise_max(m, *(const svec_t*)(b + (wy * IW + wx) * CS));
-        *(svec_t*)(out + plane * out_stride + ((int64_t)oy * Wo + ox) * C + g * N) = m;
-      }
-      return;
+        for (int wx = 0; wx < 3; ++wx)
+          if (wy || wx) m = __builtin_elementwise_max(m, *(const svec_t*)(b + (wy * IW + wx) * CS));
+      *(svec_t*)(out + plane * out_stride + ((int64_t)oy * Wo + ox) * C + g * N) = m;
     }
+    return;
   }
   for (int e = threadIdx.x; e < TPH * TPW * G; e += 256) {
     const int g = e % G, q = e / G;
@@ -349,6 +326,99 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 #pragma unroll
     for (int i = 0; i < N; ++i) r[i] = from_f32<T>(m[i]);
     *(vec_t*)(out + plane * out_stride + ((int64_t)oy * Wo + ox) * C + g * N) = r;
+  }
+}
+
+// LRN then pool for fp32 storage, C = 96 and 256 with the default window (n = 5), in registers.  A thread
+// owns four channels (one 16-byte vector) of two pooled columns and walks down SR pooled rows: per input row
+// it loads its vector and the two channels on either side of five pixels (the neighbours' loads, so
+// the repeats hit L1), forms their LRN, and keeps the row's horizontal maxima; an output row is the
+// maximum of three input rows, the top one kept from the output row above.  The next input row's loads
+// are issued before the current row's LRN.  No LDS and no barriers, every thread busy: (5 / 4) x
+// (2 SR + 1) / (2 SR) of the LRN work.  Bound by memory: 16 maps of 59 x 79 x 256 take 22 us (4.3 TB/s of
+// compulsory bytes) against 73 us with a pixel's channels split over two threads and an LDS tile (110
+// of 256 threads busy, two workgroups per CU).
+template <int C, int SR, bool MULTI>
+__global__ __launch_bounds__(256) void lrn_pool_f32_kernel(const float* __restrict__ in, float* __restrict__ out,
+                                                           KRuns runs, float alpha_n, float beta, float k) {
+  constexpr int G = C / 4, NCG = 256 / G, NC = 2, NP = 2 * NC + 1;  // vectors, column groups, columns, pixels
+  typedef float f32x2_t __attribute__((ext_vector_type(2)));
+  const int nb = gridDim.x, xcd = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
+  int bid = xcd * per + min(xcd, rem) + blockIdx.x / 8;
+  const KRun& rn = runs.r[run_of<MULTI>(runs, bid)];
+  bid -= rn.first;
+  const int H = rn.H, W = rn.W, Ho = rn.Ho, Wo = rn.Wo;
+  const int tx = bid % rn.tiles_x;
+  bid /= rn.tiles_x;
+  const int ty = bid % rn.tiles_y, plane = bid / rn.tiles_y;
+  const int grp = threadIdx.x / G, g = threadIdx.x % G;
+  const int ox = (tx * NCG + grp) * NC, oy0 = ty * SR, nrows = min(SR, Ho - oy0);
+  if (grp >= NCG || ox >= Wo) return;
+  const float* src = in + rn.in_off + plane * rn.in_stride + 4 * g;
+  float* dst = out + rn.out_off + plane * rn.out_stride + 4 * g;
+  const int lo = g > 0 ? -2 : 0, hi = g + 1 < G ? 4 : 2;  // the channels below and above (or own ones, unused)
+  struct Row {
+    f32x4 v[NP];
+    f32x2_t l[NP], r[NP];
+  };
+  // Pixels past the map repeat its last row or column, which the clipped window holds too.
+  auto load_row = [&](int y) {
+    Row a;
+    const float* row = src + (int64_t)min(y, H - 1) * W * C;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const float* q = row + (int64_t)min(2 * ox + p, W - 1) * C;
+      a.v[p] = *(const f32x4*)q;
+      a.l[p] = *(const f32x2_t*)(q + lo);
+      a.r[p] = *(const f32x2_t*)(q + hi);
+    }
+    return a;
+  };
+  struct HMax {
+    f32x4 m[NC];
+  };
+  auto row_max = [&](const Row& a) {  // horizontal maxima of the row's LRN
+    f32x4 b[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      float sq[8];  // squares of the channels from two below to two above
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        sq[i] = g > 0 ? a.l[p][i] * a.l[p][i] : 0.f;
+        sq[6 + i] = g + 1 < G ? a.r[p][i] * a.r[p][i] : 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sq[2 + i] = a.v[p][i] * a.v[p][i];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float win = ((sq[i] + sq[i + 1]) + (sq[i + 2] + sq[i + 3])) + sq[i + 4];
+        b[p][i] = a.v[p][i] * lrn_scale(win, alpha_n, beta, k);
+      }
+    }
+    HMax h;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) h.m[c][i] = fmaxf(fmaxf(b[2 * c][i], b[2 * c + 1][i]), b[2 * c + 2][i]);
+    return h;
+  };
+  Row a = load_row(2 * oy0), b = load_row(2 * oy0 + 1);
+  HMax top = row_max(a);
+  for (int i = 0; i < nrows; ++i) {
+    const int oy = oy0 + i;
+    a = load_row(2 * oy + 2);
+    const HMax mid = row_max(b);
+    b = load_row(2 * oy + 3);
+    const HMax bot = row_max(a);
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (ox + c < Wo) {
+        f32x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = fmaxf(fmaxf(fmaxf(-INFINITY, top.m[c][e]), mid.m[c][e]), bot.m[c][e]);
+        *(f32x4*)(dst + ((int64_t)oy * Wo + ox + c) * C) = r;
+      }
+    top = bot;
   }
 }
 
@@ -691,9 +761,7 @@ int run(const void* d_in, const MapRun* runs, int n_runs, int32_t C, bool lrn, b
     return (int)hipGetLastError();
   }
   if (C % N || hn > 4) return (int)hipErrorInvalidValue;
-  // Per-pixel kernel for the two channel counts of the network with the default window (n = 5).
-  // Tiles: the largest whose input pixels fit one thread each (per part) and whose LDS tile stays
-  // within 64 KB.
+  // Kernels for the two channel counts of the network with the default window (n = 5).
   if constexpr (sizeof(T) == 2) {
     if (lrn && hn == 2 && C == 256) {
       const int cfg[4] = {DN_STRIP256};
@@ -712,23 +780,39 @@ int run(const void* d_in, const MapRun* runs, int n_runs, int32_t C, bool lrn, b
       return (int)hipGetLastError();
     }
   }
-  if (lrn && hn == 2 && (C == 96 || C == 256)) {
-    // (16-bit storage reaches this only for C = 96: C = 256 takes the strip kernel above)
-    constexpr bool F32 = sizeof(T) == 4;
-    constexpr int TH96 = F32 ? 4 : DN_LRN96_TH, TW96 = F32 ? 7 : DN_LRN96_TW, TH256 = 2, TW256 = 5;
-    const int64_t blocks = C == 96 ? tiles(TH96, TW96) : tiles(TH256, TW256);
-    if (blocks <= 0) return (int)hipErrorInvalidValue;
-    // Waves per SIMD the LDS tile allows (3 and 2 workgroups of 4 waves per CU): the compiler may use
-    // the registers that occupancy leaves free for more independent work in flight.
-    if (C == 96) {
-      pixel<T, 96, F32 ? 96 : DN_LRN96_CPT, TH96, TW96, F32 ? 3 : DN_LRN96_WPE>(blocks, s, in, out, kr, an,
-                                                                               beta, k);
-    } else if constexpr (F32) {
-      pixel<T, 256, 128, TH256, TW256, 2>(blocks, s, in, out, kr, an, beta, k);
-    } else {
-      return (int)hipErrorInvalidValue;
+  if constexpr (sizeof(T) == 2) {
+    if (lrn && hn == 2 && C == 96) {
+      const int64_t blocks = tiles(DN_LRN96_TH, DN_LRN96_TW);
+      if (blocks <= 0) return (int)hipErrorInvalidValue;
+      // DN_LRN96_WPE: waves per SIMD the LDS tile allows (3 workgroups of 4 waves per CU); the compiler may
+      // use the registers that occupancy leaves free for more independent work in flight.
+      pixel<T, 96, DN_LRN96_CPT, DN_LRN96_TH, DN_LRN96_TW, DN_LRN96_WPE>(blocks, s, in, out, kr, an, beta, k);
+      return (int)hipGetLastError();
     }
-    return (int)hipGetLastError();
+  } else {
+    if (lrn && hn == 2 && (C == 96 || C == 256)) {
+      // Three pooled rows per thread, or one where that leaves CUs without a workgroup: the
+      // maps of a two-scale 227 x 227 pyramid take 3.5 us each against 6.5 at three (whose chain of rows
+      // sets the time), 16 maps of 59 x 79 x 256 18.0 us at three, 18.5 at two and four, 23 at eight.
+      const int cols = 2 * (256 / (C / 4));
+      int64_t blocks = tiles(3, cols);
+      const bool small = blocks > 0 && blocks < device_cus();
+      if (small) blocks = tiles(1, cols);
+      if (blocks <= 0) return (int)hipErrorInvalidValue;
+      auto go = [&](auto c, auto multi) {
+        constexpr int CH = decltype(c)::value;
+        constexpr bool MULTI = decltype(multi)::value;
+        if (small)
+          lrn_pool_f32_kernel<CH, 1, MULTI><<<(unsigned)blocks, 256, 0, s>>>(in, out, kr, an, beta, k);
+        else
+          lrn_pool_f32_kernel<CH, 3, MULTI><<<(unsigned)blocks, 256, 0, s>>>(in, out, kr, an, beta, k);
+      };
+      auto go2 = [&](auto multi) {
+        C == 96 ? go(std::integral_constant<int, 96>{}, multi) : go(std::integral_constant<int, 256>{}, multi);
+      };
+      n_runs == 1 ? go2(std::false_type{}) : go2(std::true_type{});
+      return (int)hipGetLastError();
+    }
   }
   int TPH, TPW;
   pick_tile<T>(C, TPH, TPW);

@@ -340,3 +340,20 @@ def test_conv1_rows_at_any_alignment(D, dt, n, H, W, shift):
     ref = D.densenet_conv_layer(1, aligned.cuda(), n, H, wide, DTS[dt], packed(D, dt))[:, :, :(W - 11) // 4 + 1]
     assert torch.isfinite(out.float()).all()
     assert torch.equal(out.view(torch.int16), ref.contiguous().view(torch.int16))
+
+
+# one clipped window; one pooled row per thread (small launches) and three, with remainders of rows, of
+# columns and of a workgroup's column groups (10 at C = 96, 4 at C = 256)
+@pytest.mark.parametrize("C,shape", [(96, (1, 2, 2)), (256, (1, 5, 8)), (96, (2, 8, 43)), (96, (24, 61, 85)),
+                                     (256, (20, 38, 39)), (256, (16, 59, 79))])
+def test_lrn_pool_f32_registers(D, C, shape):
+    """fp32 LRN then pool against fp64: sums of 5 squares, log2, exp2 and two products, a few ulp."""
+    g = torch.Generator().manual_seed(C + shape[1])
+    x = torch.randn((*shape, C), generator=g) * 40
+    out = D.densenet_lrn_pool(x.cuda(), DTS["f32"], D.net_params(alpha=1e-3)).double().cpu()
+    xx = x.double().permute(0, 3, 1, 2)
+    sq = torch.nn.functional.pad(xx * xx, (0, 0, 0, 0, 2, 2))
+    b = xx * (1.0 + 1e-3 / 5 * sum(sq[:, j:j + C] for j in range(5))) ** -0.75
+    ref = torch.nn.functional.max_pool2d(b, 3, 2, ceil_mode=True).permute(0, 2, 3, 1)
+    # log2's absolute error (an ulp of a value up to 8) times 0.75 ln 2, and about 8 roundings: 2e-6
+    assert bool(((out - ref).abs() <= 2e-6 * ref.abs() + 1e-30).all())
