@@ -580,6 +580,226 @@ __global__ __launch_bounds__((conv_threads<T, BM, TM, TS, TN_>()), OCC) void con
   }
 }
 
+// Keeps the compiler from moving this wave's LDS accesses across it (a wave's own LDS operations
+// execute in order).
+__device__ inline void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// f(integral_constant<I>) for I = B .. E - 1, in order.
+template <int B, int E, typename F>
+__device__ inline void static_for(F&& f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Stride-1 conv for 16-bit storage on small maps: the pixels of a run's planes as one sequence.
+// A 16 x 16 tile of a 13 x 13 map computes 7 MFMA pixel tiles for 169 pixels (5.3 tiles' worth), and its
+// workgroup a whole map whatever its size.  Here a workgroup takes PT consecutive pixels of the
+// sequence (plane, row, column), across row and plane boundaries, so that only the run's last MFMA
+// tile has empty pixels.
+// Halo: positions are numbered along padded planes, pad = (R - 1) / 2 zero columns left of each row and
+// pad zero rows above each plane (the zeros right of a row and below a plane are the next row's and
+// plane's), so a tap is a constant distance away and the halo of consecutive pixels is a contiguous
+// range of positions.  LDS holds the 16-byte halves (channels 0..7 and 8..15 of the chunk) of HS
+// positions in two planes: 32 consecutive pixels read 32 consecutive slots, conflict-free but for a
+// slot or two where a row ends.  Stages, weights and the order of the sums are conv_s1_direct_kernel's, so
+// the results are the same bit for bit.  Bound by the matrix cores: conv3 of 2000 windows (13 x 13 maps, bf16)
+// 566 -> 453 us (1.32 PFLOP/s), conv4 470 -> 360, conv5 292 -> 245, their conv2 (27 x 27) 787 -> 719.
+// ------------------------------------------------------------------------------------------------
+// CHUNKED: a stage is a whole chunk (all R kernel rows' weights).
+template <typename T, int R, int BM, int TM, int OCC, int BMP, int WN, int TN, int HS, bool CHUNKED, bool MULTI>
+__global__ __launch_bounds__(64 * (BM / (32 * TM)) * WN, OCC) void conv_flat_kernel(
+    const T* __restrict__ in, T* __restrict__ out, const T* __restrict__ wp, const float* __restrict__ bias,
+    KRuns runs, int C, int Cg, int M, int Mg, int mblocks) {
+  using Op = Mfma<T>;
+  using frag = typename Op::frag;
+  typedef T out4_t __attribute__((ext_vector_type(4)));
+  typedef T vec8_t __attribute__((ext_vector_type(8)));
+  constexpr int pad = (R - 1) / 2, WM = BM / (32 * TM), NW = WM * WN, PT = 32 * TN * WN;
+  static_assert(WM * 32 * TM == BM && BMP % BM == 0 && HS % 64 == 0, "whole wave tiles and load pieces");
+  constexpr int WSLOTS = R * BM * 2, WSLOTS_P = R * BMP * 2, DW = Pieces<16>::count(WSLOTS, NW);
+  static_assert(WSLOTS % 64 == 0, "a stage's weights are whole 1 KB pieces");
+  constexpr int DH = (HS / 64 + NW - 1) / NW;                     // groups of 64 positions per wave
+  constexpr int HALF_E = HS * 8, HALO_E = 2 * HALF_E, ROW_E = DW * NW * 512, W_E = CHUNKED ? R * ROW_E : ROW_E;
+  constexpr int SROW = 32 * TM + 8;                               // epilogue staging: a pixel's row
+  static_assert(NW * 32 * SROW <= 2 * HALO_E + 2 * W_E, "per-wave staging fits the stage buffers");
+  __shared__ __align__(1024) T s_mem[2 * HALO_E + 2 * W_E];
+  auto halo_buf = [&](int b) { return s_mem + b * HALO_E; };
+  auto wrow_buf = [&](int b) { return s_mem + 2 * HALO_E + b * W_E; };
+
+  const int nb = gridDim.x, xcd = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
+  int bid = xcd * per + min(xcd, rem) + blockIdx.x / 8;
+  const KRun& rn = runs.r[run_of<MULTI>(runs, bid)];
+  bid -= rn.first;
+  const int H = rn.H, W = rn.W, total = rn.tiles_y * H * W;  // tiles_y: planes; all pixels of the run
+  const int mb = bid % mblocks, p0 = (bid / mblocks) * PT;   // channel block, first pixel
+  const int mpg = Mg / BM, g = mb / mpg, m0 = (mb % mpg) * BM;
+  const int mbp = g * (Mg / BMP) + m0 / BMP, msub = m0 % BMP;
+  const int Wp = W + pad, Hp = H + pad, HW = H * W;
+  // Padded position of pixel p; a pixel's first tap (0, 0) is pad (Wp + 1) positions before it.
+  auto position = [&](int p) {
+    const int pl = p / HW, r = p - pl * HW, y = r / W, x = r - y * W;
+    return (pl * Hp + pad + y) * Wp + pad + x;
+  };
+  const int last = min(p0 + PT, total) - 1, pos0 = position(p0);
+  const int first_tap = pos0 - pad * (Wp + 1);                             // halo slot 0
+  const int nslots = position(last) - pos0 + 2 * pad * (Wp + 1) + 1;       // at most HS
+  // Loads address the run from pixel `base` on, which no pixel of the halo precedes.
+  const int base = max(p0 - pad * (Wp + 1), 0);
+  const T* src = in + rn.in_off + (int64_t)base * C + g * Cg;
+  const int64_t left = ((int64_t)(total - base) * C - g * Cg) * (int64_t)sizeof(T);
+  const __amdgpu_buffer_rsrc_t rsrc_in = uniform_rsrc(src, (uint32_t)min(left, (int64_t)0x7fffffff));
+  const T* wg = wp + (int64_t)mbp * (Cg / 16) * R * (WSLOTS_P * 8);
+  const __amdgpu_buffer_rsrc_t rsrc_w = uniform_rsrc(wg, (uint32_t)((Cg / 16) * R * WSLOTS_P * 16));
+  constexpr uint32_t OOB = 0x80000000u;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const int wm = wave % WM, wn = wave / WM;
+  const int half = lane >> 5, l32 = lane & 31;
+  auto gtile = [&](int t) { return t * WN + wn; };  // MFMA pixel tile t of this wave
+  // Groups of 64 halo positions go to the waves in turn; byte offset of this lane's position in each.
+  uint32_t hoff[DH];
+#pragma unroll
+  for (int i = 0; i < DH; ++i) {
+    const int s = (wave + NW * i) * 64 + lane, q = first_tap + s;
+    const int row = q / Wp, x = q - row * Wp - pad, pl = row / Hp, y = row - pl * Hp - pad;
+    const int p = pl * HW + y * W + x;
+    const bool ok = s < nslots && x >= 0 && y >= 0 && p < total;
+    hoff[i] = ok ? (uint32_t)(p - base) * (uint32_t)(C * (int)sizeof(T)) : OOB;
+  }
+  auto load_halo = [&](int buf, int c0) {
+#pragma unroll
+    for (int i = 0; i < DH; ++i) {
+      const int grp = wave_s + NW * i;
+      if (grp * 64 < nslots) {
+        lds_direct16(rsrc_in, halo_buf(buf) + grp * 512, hoff[i], (uint32_t)(c0 * sizeof(T)));
+        lds_direct16(rsrc_in, halo_buf(buf) + HALF_E + grp * 512, hoff[i], (uint32_t)(c0 * sizeof(T)) + 16u);
+      }
+    }
+  };
+  const uint32_t lane16 = (uint32_t)lane * 16u;
+  auto load_w = [&](T* row, int c0, int ky) {  // as conv_s1_direct_kernel
+    const uint32_t add = (uint32_t)(((c0 / 16) * R + ky) * WSLOTS_P * 16);
+#pragma unroll
+    for (int i = 0; i < DW; ++i) {
+      const int p = wave_s * DW + i;
+      const uint32_t from = BMP == BM ? (uint32_t)p * 1024u
+                                      : (uint32_t)(((p / (BM / 32)) * BMP + msub + 32 * (p % (BM / 32))) * 32);
+      if (p * 64 < WSLOTS) lds_direct16(rsrc_w, row + p * 512, lane16, add + from);
+    }
+  };
+
+  int pix[TN];  // LDS element offset of this lane's pixel's first tap, in the half it reads
+  int tnv = 0;  // MFMA pixel tiles of this wave with a pixel: a prefix
+#pragma unroll
+  for (int t = 0; t < TN; ++t) {
+    pix[t] = (position(min(p0 + gtile(t) * 32 + l32, last)) - pos0) * 8 + half * HALF_E;
+    tnv += p0 + gtile(t) * 32 <= last ? 1 : 0;
+  }
+  tnv = __builtin_amdgcn_readfirstlane(tnv);
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int t = 0; t < TN; ++t) acc[a][t] = f32x16{};
+
+  const int nchunks = Cg / 16, nst = nchunks * R;
+  auto stage_loop = [&](auto tnv_c) {
+    constexpr int TNV = decltype(tnv_c)::value;
+    auto row_taps = [&](const T* halo, const T* ws, int ky) {
+      if constexpr (TNV > 0) {
+        const T* hs = halo + ky * Wp * 8;
+#pragma unroll
+        for (int kx = 0; kx < R; ++kx) {
+          frag x[TNV], w[TM];
+#pragma unroll
+          for (int t = 0; t < TNV; ++t) x[t] = lds_frag16<T>(hs + pix[t] + kx * 8);
+#pragma unroll
+          for (int mt = 0; mt < TM; ++mt) {
+            const int m = wm * 32 * TM + mt * 32 + l32;
+            w[mt] = lds_frag16<T>(ws + (kx * BM + m) * 16 + (half ^ ((m >> 4) & 1)) * 8);
+          }
+#pragma unroll
+          for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+            for (int t = 0; t < TNV; ++t) acc[mt][t] = Op::mma(w[mt], x[t], acc[mt][t]);
+        }
+      }
+    };
+    if constexpr (CHUNKED) {
+      auto load = [&](int chunk) {
+        load_halo(chunk & 1, chunk * 16);
+#pragma unroll
+        for (int ky = 0; ky < R; ++ky) load_w(wrow_buf(chunk & 1) + ky * ROW_E, chunk * 16, ky);
+      };
+      load(0);
+      wait_vmem();
+      __syncthreads();
+      for (int chunk = 0; chunk < nchunks; ++chunk) {
+        if (chunk + 1 < nchunks) load(chunk + 1);
+#pragma unroll
+        for (int ky = 0; ky < R; ++ky) row_taps(halo_buf(chunk & 1), wrow_buf(chunk & 1) + ky * ROW_E, ky);
+        wait_vmem();
+        __syncthreads();
+      }
+    } else {
+      load_halo(0, 0);
+      load_w(wrow_buf(0), 0, 0);
+      wait_vmem();
+      __syncthreads();
+      for (int st = 0; st < nst; ++st) {
+        const int chunk = st / R, ky = st - chunk * R;
+        if (st + 1 < nst) load_w(wrow_buf((st + 1) & 1), ((st + 1) / R) * 16, (st + 1) % R);
+        if (ky == 0 && chunk + 1 < nchunks) load_halo((chunk + 1) & 1, (chunk + 1) * 16);
+        row_taps(halo_buf(chunk & 1), wrow_buf(st & 1), ky);
+        wait_vmem();
+        __syncthreads();
+      }
+    }
+  };
+  static_assert(TN >= 1 && TN <= 4, "stage loop variants cover 0..4 tiles");
+  switch (tnv) {
+    case 4: if constexpr (TN >= 4) stage_loop(std::integral_constant<int, 4>{}); break;
+    case 3: if constexpr (TN >= 3) stage_loop(std::integral_constant<int, 3>{}); break;
+    case 2: if constexpr (TN >= 2) stage_loop(std::integral_constant<int, 2>{}); break;
+    case 1: stage_loop(std::integral_constant<int, 1>{}); break;
+    default: stage_loop(std::integral_constant<int, 0>{}); break;
+  }
+
+  // Epilogue: each wave stages one MFMA pixel tile at a time in a private LDS region and writes its
+  // pixels' rows of 32 TM channels as 16-byte chunks.  The pixels' outputs are consecutive in memory.
+  constexpr int NCH = 4 * TM;
+  T* stg = s_mem + wave * (32 * SROW);
+  const int mw = g * Mg + m0 + wm * 32 * TM;  // this wave's first output channel
+  T* dst = out + rn.out_off + (int64_t)p0 * M + mw;
+#pragma unroll
+  for (int t = 0; t < TN; ++t) {
+    wave_lds_order();
+#pragma unroll
+    for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int m = mt * 32 + 8 * q + 4 * half;
+        const f32x4 bv = *(const f32x4*)(bias + mw + m);
+        out4_t o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = from_f32<T>(fmaxf(acc[mt][t][4 * q + e] + bv[e], 0.f));
+        *(out4_t*)(stg + l32 * SROW + m) = o;
+      }
+    wave_lds_order();
+#pragma unroll
+    for (int it = 0; it < NCH / 2; ++it) {  // 32 pixels x NCH chunks over 64 lanes
+      const int u = it * 64 + lane, p = u / NCH, ch = u % NCH;
+      const vec8_t v = *(const vec8_t*)(stg + p * SROW + 8 * ch);
+      const int idx = gtile(t) * 32 + p;
+      if (p0 + idx <= last) store_out(v, (vec8_t*)(dst + (int64_t)idx * M + 8 * ch));
+    }
+  }
+}
+
 // ------------------------------------------------------------------------------------------------
 // Stride-1 conv for fp32 storage on the bf16 matrix cores.  An fp32 value is split into three bf16
 // values, x = h + m + l + d with |d| <= 2^-27 |x| (each the nearest bf16 of what is left), and a product
@@ -614,19 +834,6 @@ struct SplitCfg {
   static_assert(NW * 64 * 64 * 2 <= LDS_E, "the fp32 epilogue staging fits the stage buffers");
   static_assert((size_t)LDS_E * 2 <= 80 * 1024, "two workgroups per CU");
 };
-
-// Keeps the compiler from moving this wave's LDS accesses across it (a wave's own LDS operations
-// execute in order).
-__device__ inline void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
-// f(integral_constant<I>) for I = B .. E - 1, in order.
-template <int B, int E, typename F>
-__device__ inline void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
 
 // ksplit > 1 (launches too small to fill the chip): the launch is ksplit copies of its base workgroups;
 // copy ks runs the input-channel chunks [ks nchunks / ksplit, (ks + 1) nchunks / ksplit) and writes its
@@ -1596,6 +1803,83 @@ int run_conv_s1(const T* in, T* out, const T* wstage, const float* bias, const M
   return (int)hipGetLastError();
 }
 
+// Halo positions of PT pixels of a run's sequence, at most: the pixels, the pads of the row and plane
+// ends between them, and the taps of the first and the last.
+template <int R>
+int64_t flat_positions(const MapRun& r, int64_t PT) {
+  constexpr int64_t pad = (R - 1) / 2;
+  const int64_t HW = (int64_t)r.H * r.W, rows = (PT - 2) / r.W + 1, planes = r.n > 1 ? (PT - 2) / HW + 1 : 0;
+  return PT + rows * pad + planes * pad * (r.W + pad) + 2 * pad * (r.W + pad + 1) + 1;
+}
+
+// Whether conv_flat_kernel can take a launch's runs in workgroups of PT pixels with HS halo positions: the
+// planes of a run follow one another, and the halos fit.
+template <int R, int PT, int HS>
+bool flat_fits(const MapRun* runs, int n_runs, int C, int M) {
+  for (int i = 0; i < n_runs; ++i) {
+    const MapRun& r = runs[i];
+    const int64_t HW = (int64_t)r.H * r.W;
+    if (r.n <= 0 || r.n * HW > 0x3fffffffLL || (r.n > 1 && (r.in_stride != HW * C || r.out_stride != HW * M)) ||
+        flat_positions<R>(r, PT) > HS)
+      return false;
+  }
+  return true;
+}
+
+// Whether TS tiles would compute at least a tenth more MFMA pixel tiles than the pixels as sequences (where
+// both compute about the same, the 2-D tiles' smaller halos win: one image's 74 x 74 maps, conv3 58 us in
+// tiles and 73 as sequences).
+template <int TS>
+bool flat_fills_better(const MapRun* runs, int n_runs) {
+  constexpr int TH = TS / 100, TW = TS % 100;
+  int64_t tiled = 0, flat = 0;
+  for (int i = 0; i < n_runs; ++i) {
+    int64_t one = 0;
+    for (int y = 0; y < runs[i].H; y += TH)
+      for (int x = 0; x < runs[i].W; x += TW) {
+        const int rows = (std::min(TH, runs[i].H - y) + 1) / 2 * (TW / 16), cols = (std::min(TW, runs[i].W - x) + 1) / 2;
+        one += TH == 16 ? std::min(rows, cols) : rows;
+      }
+    tiled += one * runs[i].n;
+    flat += ((int64_t)runs[i].n * runs[i].H * runs[i].W + 31) / 32;
+  }
+  return 10 * tiled >= 11 * flat;
+}
+
+// Workgroups of PT pixels x BM channels of a launch's runs as sequences.
+int64_t flat_blocks(const MapRun* runs, int n_runs, int M, int PT, int BM) {
+  int64_t tiles = 0;
+  for (int i = 0; i < n_runs; ++i) tiles += ((int64_t)runs[i].n * runs[i].H * runs[i].W + PT - 1) / PT;
+  return tiles * (M / BM);
+}
+
+template <typename T, int R, int BM, int TM, int OCC, int BMP, int WN, int TN, int HS, bool CHUNKED = false>
+int run_conv_flat(const T* in, T* out, const T* wstage, const float* bias, const MapRun* runs, int n_runs, int C,
+                  int G, int M, hipStream_t s) {
+  constexpr int PT = 32 * TN * WN, NT = 64 * (BM / (32 * TM)) * WN;
+  const int Cg = C / G, Mg = M / G;
+  if (Mg % BM || n_runs <= 0 || n_runs > MAX_RUNS) return (int)hipErrorInvalidValue;
+  const int mblocks = G * (Mg / BM);
+  MapRun one[MAX_RUNS];  // each run as one sequence
+  for (int i = 0; i < n_runs; ++i) one[i] = runs[i], one[i].n = 1;
+  KRuns kr;
+  int i = 0;
+  const int64_t blocks = fill_kruns(one, n_runs, kr, [&](KRun& k) {
+    k.Ho = k.H, k.Wo = k.W;
+    k.tiles_y = runs[i++].n;
+    k.tiles_x = (int)(((int64_t)k.tiles_y * k.H * k.W + PT - 1) / PT);
+    return (int64_t)k.tiles_x * mblocks;
+  });
+  if (blocks <= 0) return (int)hipErrorInvalidValue;
+  if (n_runs == 1)
+    conv_flat_kernel<T, R, BM, TM, OCC, BMP, WN, TN, HS, CHUNKED, false><<<(unsigned)blocks, NT, 0, s>>>(
+        in, out, wstage, bias, kr, C, Cg, M, Mg, mblocks);
+  else
+    conv_flat_kernel<T, R, BM, TM, OCC, BMP, WN, TN, HS, CHUNKED, true><<<(unsigned)blocks, NT, 0, s>>>(
+        in, out, wstage, bias, kr, C, Cg, M, Mg, mblocks);
+  return (int)hipGetLastError();
+}
+
 // Per layer: channel block BM, MFMA tiles per wave along channels TM, waves per SIMD requested, and
 // the tile shape (100 rows + columns).  Chosen by timing each layer at the 96-plane batch shapes: two waves per
 // SIMD matter most; conv3/conv5 run best at three waves per SIMD; conv4's 192 channels per group run
@@ -1740,19 +2024,42 @@ int conv_dispatch(int layer, const void* d_in, const MapRun* runs, int n_runs, c
     }
 #define DN_RUN_ARGS in, out, ws, bias, runs, n_runs, L_C[li], L_G[li], L_M[li], s
 #define DN_SMALL_CFG(l) 3, 64, 2, DN_SMALL_OCC, 1616, L_BM[l], DN_SMALL_TN
+#define DN_FLAT_ARGS runs, n_runs, L_C[li], L_M[li]
+    // Maps that fill their tiles badly go as sequences where the launch keeps the chip busy that way (2000,
+    // 350 and 100 windows' 13 x 13 maps: conv3 566 -> 453, 112 -> 91 and 37 -> 32 us; 200 windows' 27 x 27
+    // maps: conv2 85 -> 79 us).  With fewer workgroups than the limits the tiles' larger number wins (100
+    // windows: conv5 25 us as sequences, 22 in tiles; 60 windows: conv2 30 against 27).
+    const int64_t cus = device_cu_count();
+    const bool fills = layer == 2 ? flat_fills_better<1632>(runs, n_runs) : flat_fills_better<1616>(runs, n_runs);
     switch (layer) {
       case 2:
+        if (fills && flat_fits<5, 512, 832>(DN_FLAT_ARGS) && flat_blocks(runs, n_runs, 256, 512, 64) >= 4 * cus)
+          return run_conv_flat<T, 5, 64, 2, 2, L_BM[1], 4, 4, 832>(DN_RUN_ARGS);
         return run_conv_s1<T, 5, DN_CONV2_CFG>(DN_RUN_ARGS);
+      // Layers 3 to 5: launches of at most two small workgroups (128 pixels x 64 channels, waves of 32
+      // pixels, whole chunks per stage) per CU take those, which spread the pixels evenly over the
+      // CUs: the eight maps of a 480 x 640 image's pyramid (49 x 65 .. 15 x 20) 30 -> 25, 25 -> 20 and 19.5 ->
+      // 17.5 us, 20 windows' maps 23 -> 13, 18 -> 11 and 18 -> 10 us against 16 x 16 tiles.
+#define DN_LAYER3(l, cfg, ...)                                                                              \
+  if (flat_blocks(runs, n_runs, L_M[li], 128, 64) <= 2 * cus && flat_fits<3, 128, 320>(DN_FLAT_ARGS))       \
+    return run_conv_flat<T, 3, 64, 2, 2, L_BM[l], 4, 1, 320, true>(DN_RUN_ARGS);                            \
+  if (fills && flat_fits<3, 256, 384>(DN_FLAT_ARGS)) {                                                      \
+    if (!small_launch<cfg>(runs, n_runs, L_M[li]))                                                          \
+      return run_conv_flat<T, 3, __VA_ARGS__, L_BM[l], 2, 4, 384>(DN_RUN_ARGS);                             \
+    if (2 * flat_blocks(runs, n_runs, L_M[li], 256, 64) >= 3 * cus)                                         \
+      return run_conv_flat<T, 3, 64, 2, 3, L_BM[l], 4, 2, 384>(DN_RUN_ARGS);                                \
+  }                                                                                                         \
+  if (small_launch<cfg>(runs, n_runs, L_M[li])) return run_conv_s1<T, DN_SMALL_CFG(l)>(DN_RUN_ARGS);        \
+  return run_conv_s1<T, 3, cfg>(DN_RUN_ARGS);
       case 3:
-        if (small_launch<DN_CONV3_CFG>(runs, n_runs, L_M[li])) return run_conv_s1<T, DN_SMALL_CFG(2)>(DN_RUN_ARGS);
-        return run_conv_s1<T, 3, DN_CONV3_CFG>(DN_RUN_ARGS);
+        DN_LAYER3(2, DN_CONV3_CFG, 128, 2, 3)
       case 4:
-        if (small_launch<DN_CONV4_CFG>(runs, n_runs, L_M[li])) return run_conv_s1<T, DN_SMALL_CFG(3)>(DN_RUN_ARGS);
-        return run_conv_s1<T, 3, DN_CONV4_CFG>(DN_RUN_ARGS);
+        DN_LAYER3(3, DN_CONV4_CFG, 192, 3, 2)
       case 5:
-        if (small_launch<DN_CONV5_CFG>(runs, n_runs, L_M[li])) return run_conv_s1<T, DN_SMALL_CFG(4)>(DN_RUN_ARGS);
-        return run_conv_s1<T, 3, DN_CONV5_CFG>(DN_RUN_ARGS);
+        DN_LAYER3(4, DN_CONV5_CFG, 128, 2, 3)
+#undef DN_LAYER3
     }
+#undef DN_FLAT_ARGS
 #undef DN_SMALL_CFG
 #undef DN_RUN_ARGS
     return (int)hipErrorInvalidValue;

@@ -357,3 +357,29 @@ def test_lrn_pool_f32_registers(D, C, shape):
     ref = torch.nn.functional.max_pool2d(b, 3, 2, ceil_mode=True).permute(0, 2, 3, 1)
     # log2's absolute error (an ulp of a value up to 8) times 0.75 ln 2, and about 8 roundings: 2e-6
     assert bool(((out - ref).abs() <= 2e-6 * ref.abs() + 1e-30).all())
+
+
+# Launches of many small maps: pixels as sequences across rows and planes, in each of its configurations
+# (layer 2 and layers 3 to 5 large; 3 to 5 medium; at most two workgroups per CU), with maps of one row or
+# column, planes shorter than a workgroup's pixels and a partly filled last workgroup.
+@pytest.mark.parametrize("layer,n,H,W", [(2, 200, 27, 27), (2, 900, 11, 19), (3, 700, 13, 13), (4, 700, 13, 13),
+                                         (5, 1100, 13, 13), (3, 150, 13, 13), (4, 64, 17, 23), (5, 200, 13, 14),
+                                         (3, 40, 13, 13), (5, 7, 1, 40), (4, 5, 33, 1), (3, 2, 60, 60)])
+def test_conv_pixel_sequences(D, layer, n, H, W):
+    """Sampled planes equal, bit for bit, the same plane computed in a launch of its own (whose workgroups
+    hold other pixels of it), and the first and last equal fp64 to bf16's rounding."""
+    g = torch.Generator().manual_seed(layer * 1000 + n)
+    C = LAYERS[layer - 1][1]
+    x = (torch.randn((n, H, W, C), generator=g) * 20).clamp(min=0).to(torch.bfloat16).cuda()
+    pk = packed(D, "bf16")
+    out = D.densenet_conv_layer(layer, x, n, H, W, DTS["bf16"], pk)
+    for i in sorted({0, 1, n // 3, n // 2, n - 2, n - 1}):
+        one = D.densenet_conv_layer(layer, x[i:i + 1].contiguous(), 1, H, W, DTS["bf16"], pk)
+        assert torch.equal(one[0].view(torch.int16), out[i].view(torch.int16)), f"plane {i}"
+    w, b = (torch.from_numpy(v) for v in W7[layer - 1])
+    _, _, R, s, p, G = LAYERS[layer - 1]
+    for i in (0, n - 1):
+        ref = torch.nn.functional.conv2d(x[i:i + 1].double().cpu().permute(0, 3, 1, 2), w.bfloat16().double(),
+                                         b.double(), s, p, 1, G).clamp(min=0).permute(0, 2, 3, 1)[0]
+        # half an ulp of bf16 (2^-9 relative to the value's binade: 2^-8 of the value) and fp32 sums
+        assert bool(((out[i].double().cpu() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-3).all())
