@@ -577,7 +577,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 // instead and leaves the loads of one phase alone in flight; one thread per output element with its
 // whole channel window repeats every load 2 HN + 1 times over.  64 maps of 55 x 55 x 96 in fp16, pool
 // then LRN: 10.4 us (4.4 TB/s of compulsory bytes; 103 us by element).  2000 maps of 13 x 13 x 256 in
-// bf16, pool alone: 28 us (7.5 TB/s with the input partly cached; 118 us through an LDS tile).
+// bf16, pool alone: 41 us (5.1 TB/s; 118 us through an LDS tile).
 // HN: half the LRN's channel window, or -1 for pooling alone.
 template <typename T, int HN>
 __global__ __launch_bounds__(256) void pool_vector_kernel(const T* __restrict__ in, T* __restrict__ out,
