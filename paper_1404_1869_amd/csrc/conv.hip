@@ -1818,13 +1818,16 @@ int64_t flat_positions(const MapRun& r, int64_t PT) {
 }
 
 // Whether conv_flat_kernel can take a launch's runs in workgroups of PT pixels with HS halo positions: the
-// planes of a run follow one another, and the halos fit.
+// planes of a run follow one another, the padded positions count in 32 bits, and the halos fit.  Planes of 2^31
+// bytes go to run_conv_s1, which refuses them.
 template <int R, int PT, int HS>
 bool flat_fits(const MapRun* runs, int n_runs, int C, int M) {
+  constexpr int64_t pad = (R - 1) / 2;
   for (int i = 0; i < n_runs; ++i) {
     const MapRun& r = runs[i];
     const int64_t HW = (int64_t)r.H * r.W;
-    if (r.n <= 0 || r.n * HW > 0x3fffffffLL || (r.n > 1 && (r.in_stride != HW * C || r.out_stride != HW * M)) ||
+    if (r.n <= 0 || r.n > 0x3fffffffLL / ((r.H + pad) * (r.W + pad)) || HW * C * 2 >= 0x7fffffffLL ||
+        (r.n > 1 && (r.in_stride != HW * C || r.out_stride != HW * M)) ||
         flat_positions<R>(r, PT) > HS)
       return false;
   }

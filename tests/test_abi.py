@@ -264,6 +264,18 @@ def test_region_map_size_limit():
                                      ctypes.c_float(227.0), 6, fake, fake, None, None) == D.DN_OK
 
 
+@pytest.mark.parametrize("layer,C", [(2, 96), (3, 256), (4, 384), (5, 384)])
+@pytest.mark.parametrize("W", [9, 10, 13, 16])
+def test_conv_layer_plane_size_limit(layer, C, W):
+    """conv2-5 address one 16-bit plane with 32-bit byte offsets: a plane of 2^31 - 1 bytes or more is refused
+    before any launch, also at the widths whose pixels run as one sequence."""
+    L = D.lib()
+    fake = ctypes.c_void_p(256)
+    for H in (-(-0x7fffffff // (W * C * 2)), 2 * 0x7fffffff // (W * C * 2)):
+        st = L.densenet_conv_layer(layer, fake, 1, H, W, D.DN_F16, fake, fake, None)
+        assert st != D.DN_OK and "invalid argument" in D.last_error(), (H, D.last_error())
+
+
 def _conv_query(L, descs, dt, net):
     n = len(descs)
     pd = (D.dn_plane_desc * n)(*descs)
