@@ -1795,10 +1795,6 @@ int run_conv_s1(const T* in, T* out, const T* wstage, const float* bias, const M
     return (int64_t)k.tiles_x * k.tiles_y * mblocks;
   });
   if (blocks <= 0) return (int)hipErrorInvalidValue;
-  // buffer descriptors address one plane with 32-bit byte offsets
-  for (int i = 0; i < n_runs; ++i)
-    if ((int64_t)runs[i].H * runs[i].W * C * (int64_t)sizeof(T) >= 0x7fffffffLL)
-      return (int)hipErrorInvalidValue;
   if (n_runs == 1)
     conv_s1_direct_kernel<T, R, BM, TM, OCC, TS, BMP, TN, false><<<(unsigned)blocks, Cf::NT, 0, s>>>(
         in, out, wstage, bias, kr, C, Cg, M, Mg, mblocks);
@@ -1818,15 +1814,14 @@ int64_t flat_positions(const MapRun& r, int64_t PT) {
 }
 
 // Whether conv_flat_kernel can take a launch's runs in workgroups of PT pixels with HS halo positions: the
-// planes of a run follow one another, the padded positions count in 32 bits, and the halos fit.  Planes of 2^31
-// bytes go to run_conv_s1, which refuses them.
+// planes of a run follow one another, the padded positions count in 32 bits, and the halos fit.
 template <int R, int PT, int HS>
 bool flat_fits(const MapRun* runs, int n_runs, int C, int M) {
   constexpr int64_t pad = (R - 1) / 2;
   for (int i = 0; i < n_runs; ++i) {
     const MapRun& r = runs[i];
     const int64_t HW = (int64_t)r.H * r.W;
-    if (r.n <= 0 || r.n > 0x3fffffffLL / ((r.H + pad) * (r.W + pad)) || HW * C * 2 >= 0x7fffffffLL ||
+    if (r.n <= 0 || r.n > 0x3fffffffLL / ((r.H + pad) * (r.W + pad)) ||
         (r.n > 1 && (r.in_stride != HW * C || r.out_stride != HW * M)) ||
         flat_positions<R>(r, PT) > HS)
       return false;
@@ -1840,16 +1835,20 @@ bool flat_fits(const MapRun* runs, int n_runs, int C, int M) {
 template <int TS>
 bool flat_fills_better(const MapRun* runs, int n_runs) {
   constexpr int TH = TS / 100, TW = TS % 100;
+  // MFMA pixel tiles of a tile holding rv x cv pixels of the map
+  auto mfma_tiles = [](int rv, int cv) {
+    const int64_t rows = (rv + 1) / 2 * (TW / 16), cols = (cv + 1) / 2;
+    return TH == 16 ? std::min(rows, cols) : rows;
+  };
   int64_t tiled = 0, flat = 0;
   for (int i = 0; i < n_runs; ++i) {
-    int64_t one = 0;
-    for (int y = 0; y < runs[i].H; y += TH)
-      for (int x = 0; x < runs[i].W; x += TW) {
-        const int rows = (std::min(TH, runs[i].H - y) + 1) / 2 * (TW / 16), cols = (std::min(TW, runs[i].W - x) + 1) / 2;
-        one += TH == 16 ? std::min(rows, cols) : rows;
-      }
-    tiled += one * runs[i].n;
-    flat += ((int64_t)runs[i].n * runs[i].H * runs[i].W + 31) / 32;
+    const MapRun& r = runs[i];
+    const int64_t ty = r.H / TH, tx = r.W / TW;  // whole tiles down and across; then what is left of each
+    const int rv = r.H % TH, cv = r.W % TW;
+    const int64_t one = ty * tx * mfma_tiles(TH, TW) + (cv ? ty * mfma_tiles(TH, cv) : 0) +
+                        (rv ? tx * mfma_tiles(rv, TW) : 0) + (rv && cv ? mfma_tiles(rv, cv) : 0);
+    tiled += one * r.n;
+    flat += ((int64_t)r.n * r.H * r.W + 31) / 32;
   }
   return 10 * tiled >= 11 * flat;
 }
@@ -2030,6 +2029,10 @@ int conv_dispatch(int layer, const void* d_in, const MapRun* runs, int n_runs, c
       *part_need = 0;
       return 0;
     }
+    // The 16-bit kernels address one plane with 32-bit byte offsets.  Refused first: the counts below are
+    // then of maps below 2^31 bytes.
+    for (int i = 0; i < n_runs; ++i)
+      if ((int64_t)runs[i].H * runs[i].W > 0x7ffffffeLL / (L_C[li] * (int64_t)sizeof(T))) return (int)hipErrorInvalidValue;
 #define DN_RUN_ARGS in, out, ws, bias, runs, n_runs, L_C[li], L_G[li], L_M[li], s
 #define DN_SMALL_CFG(l) 3, 64, 2, DN_SMALL_OCC, 1616, L_BM[l], DN_SMALL_TN
 #define DN_FLAT_ARGS runs, n_runs, L_C[li], L_M[li]

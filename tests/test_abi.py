@@ -3,6 +3,8 @@ include/densenet.h declares, and rejects bad arguments on the host before any de
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -274,6 +276,19 @@ def test_conv_layer_plane_size_limit(layer, C, W):
     for H in (-(-0x7fffffff // (W * C * 2)), 2 * 0x7fffffff // (W * C * 2)):
         st = L.densenet_conv_layer(layer, fake, 1, H, W, D.DN_F16, fake, fake, None)
         assert st != D.DN_OK and "invalid argument" in D.last_error(), (H, D.last_error())
+
+
+@pytest.mark.parametrize("layer", [2, 3, 4, 5])
+def test_conv_layer_refuses_huge_maps_at_once(layer):
+    """Sides up to 2^31 - 1, alone and together: refused before the host counts any of their tiles."""
+    sides = [(0x7fffffff, 1), (1, 0x7fffffff), (0x7fffffff, 0x7fffffff), (10 ** 6, 10 ** 6), (0x7fffffff, 13)]
+    code = ("import ctypes\nfrom paper_1404_1869_amd import densenet as D\nL, fake = D.lib(), ctypes.c_void_p(256)\n"
+            f"for dt in (D.DN_F16, D.DN_BF16):\n  for H, W in {sides}:\n"
+            f"    st = L.densenet_conv_layer({layer}, fake, 1, H, W, dt, fake, fake, None)\n"
+            "    assert st != D.DN_OK and 'invalid argument' in D.last_error(), (H, W, D.last_error())\n"
+            "print('refused')\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "refused" in r.stdout, r.stderr
 
 
 def _conv_query(L, descs, dt, net):
