@@ -809,8 +809,10 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * WN, OCC) void conv_flat_ker
 // accumulators of their own, so the sum of the large terms is rounded once per 16 k (the fp32 MFMA
 // rounds it once per 2 k).
 // Values that do not split (infinities, NaN, and finite values that round to a bf16 infinity) are seen
-// as they are staged (inputs) or packed (weights); a workgroup that meets one computes its outputs
-// again from the fp32 data with scalar FMAs, which follow the fp32 rules.
+// as they are staged (inputs) or packed (weights); a workgroup that meets one computes its sums
+// from the fp32 data with fp32 MFMAs instead (after its split sums; at once where a weight is the cause).  An
+// infinite weight: conv3 on 8 maps of 37 x 49 524 us, conv2 on 8 of 59 x 79 282, conv1 on 8 planes of 480 x 640
+// 199, against 164, 128 and 88 us where all values split, and 51, 47 and 12 ms with one thread per pixel.
 //
 // Workgroup: 16 x 16 output pixels x 64 channels of one group, four waves of 64 channels x 64 pixels.
 // LDS holds one halo of 16 input channels as three bf16 planes, and two buffers of three taps' weights,
@@ -821,6 +823,11 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * WN, OCC) void conv_flat_ker
 // (146 TFLOP/s of fp32 work, 0.88 PFLOP/s of bf16 products), conv2 of a 480 x 640 image's 8-scale pyramid
 // 624 -> 141 us; error against 64 bits 7.1e-7 -> 2.6e-7 of the 2-norm.
 // ------------------------------------------------------------------------------------------------
+// One fp32 MFMA: two k, offset lane / 32; the accumulator's layout is the 16-bit tile's.
+__device__ inline f32x16 mma_f32(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
 template <int R>
 struct SplitCfg {
   using Cf = ConvCfg<__bf16, R, 64, 2, 1616, 2>;
@@ -841,17 +848,18 @@ struct SplitCfg {
 // split_reduce_kernel then adds the copies in order.
 // wsplit: per block of 64 output channels, chunk of 16 input channels and tap: [3][64][2 slots] of bf16,
 // in the order of the LDS buffer.  w: the fp32 weights [M][R R][Cg] and special: whether any of them
-// does not split.  scalar: compute with scalar FMAs only (maps whose tiles exceed 32-bit byte offsets).
+// does not split.  wide: fp32 MFMAs only (maps whose tiles exceed 32-bit byte offsets).
 template <int R, bool MULTI>
 __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
     const float* __restrict__ in, float* __restrict__ out, const __bf16* __restrict__ wsplit,
     const float* __restrict__ w, const uint32_t* __restrict__ special, const float* __restrict__ bias,
     KRuns runs, int C, int Cg, int M, int Mg, int mblocks, int ksplit, int base, float* __restrict__ part,
-    int64_t part_slice, int scalar) {
+    int64_t part_slice, int wide) {
   using P = SplitCfg<R>;
   using Cf = typename P::Cf;
   using Op = Mfma<__bf16>;
   using frag = typename Op::frag;
+  const bool exact = *special || wide;  // no split at all
   typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
   constexpr int pad = (R - 1) / 2, TM = P::TM, TN = P::TN, RR = R * R;
   __shared__ __align__(1024) __bf16 s_mem[P::LDS_E];
@@ -882,7 +890,7 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
   constexpr uint32_t OOB = 0x80000000u;
 
   // Halo loads: 4 channels of a pixel each, at byte offsets from the tile's first halo row in the map
-  // (a tile's rows span less than 2^31 bytes, or `scalar` is set).
+  // (a tile's rows span less than 2^31 bytes, or `wide` is set).
   const int iy_first = max(oy0 - pad, 0);
   const float* row0 = src + (int64_t)iy_first * W * C;
   const int64_t span = (int64_t)(min(oy0 + Cf::TH + pad, H) - iy_first) * W * C - g * Cg;
@@ -1023,33 +1031,68 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
       });
     }
   };
-  if (!scalar) switch (tnv) {
+  if (!exact) switch (tnv) {
     case 2: chunks(std::integral_constant<int, 2>{}); break;
     case 1: chunks(std::integral_constant<int, 1>{}); break;
     default: chunks(std::integral_constant<int, 0>{}); break;
   }
 
+  if (__syncthreads_or(top >= SPLIT_LIMIT) || exact) {
+    // Some value does not split: this workgroup's sums on the fp32 matrix cores (32x32x2), from the fp32
+    // data with 64-bit addresses.  Per chunk the halo is staged as floats; each lane takes 8 channels of
+    // its pixel (LDS) and of its output channel (weights, from L2), one per MFMA.
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    float* s_halo = (float*)s_mem;
+    constexpr int PSF = 20;  // floats per halo pixel: 16 channels, padded so that pixels fall on other banks
+    static_assert(Cf::HH * Cf::HW * PSF * 2 <= P::LDS_E, "the fp32 halo fits the stage buffers");
+#pragma unroll
+    for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+      for (int t = 0; t < TN; ++t) big[mt][t] = f32x16{}, small[mt][t] = f32x16{};
+    const float* wl = w + (int64_t)(g * Mg + m0 + l32) * RR * Cg + 8 * half;
+    for (int c0 = 16 * c_lo; c0 < 16 * c_hi; c0 += 16) {
+      __syncthreads();
+      for (int e = tid; e < P::HALO_V; e += P::NT) {
+        const int v = e & 3, p = e >> 2;
+        const int iy = oy0 - pad + p / Cf::HW, ix = ox0 - pad + p % Cf::HW;
+        v4 x = v4{};
+        if (iy >= 0 && iy < H && ix >= 0 && ix < W) {
+          const float* q = src + ((int64_t)iy * W + ix) * C + c0 + 4 * v;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x[i] = q[i];
+        }
+        *(v4*)(s_halo + p * PSF + 4 * v) = x;
+      }
+      __syncthreads();
+#pragma unroll R
+      for (int tap = 0; tap < RR; ++tap) {
+        v4 xv[TN][2], wv[TM][2];
+#pragma unroll
+        for (int t = 0; t < TN; ++t) {
+          const int idx = gtile(t) * 32 + l32;
+          const float* q = s_halo + ((out_row(idx) + tap / R) * Cf::HW + out_col(idx) + tap % R) * PSF + 8 * half;
+          xv[t][0] = *(const v4*)q, xv[t][1] = *(const v4*)(q + 4);
+        }
+#pragma unroll
+        for (int mt = 0; mt < TM; ++mt) {
+          const float* q = wl + ((int64_t)mt * 32 * RR + tap) * Cg + c0;
+          wv[mt][0] = *(const v4*)q, wv[mt][1] = *(const v4*)(q + 4);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+              big[mt][t] = mma_f32(wv[mt][i >> 2][i & 3], xv[t][i >> 2][i & 3], big[mt][t]);
+      }
+    }
+    __syncthreads();
+  }
+
   const bool raw = ksplit > 1;  // raw sums of this copy
   float* dst = (raw ? part + ks * part_slice : out) + rn.out_off + plane * rn.out_stride;
   const int mw = g * Mg + m0;  // first output channel
-  if (__syncthreads_or(top >= SPLIT_LIMIT) || *special || scalar) {
-    // Some value does not split: this workgroup's outputs in fp32, one pixel per thread.
-    const int oy = oy0 + tid / 16, ox = ox0 + tid % 16;
-    if (oy >= H || ox >= W) return;
-    for (int m = 0; m < P::BM; ++m) {
-      const float* wm = w + (int64_t)(mw + m) * RR * Cg;
-      float acc = 0.f;
-      for (int c = 16 * c_lo; c < 16 * c_hi; ++c)
-        for (int t = 0; t < RR; ++t) {
-          const int iy = oy + t / R - pad, ix = ox + t % R - pad;
-          const float x = iy >= 0 && iy < H && ix >= 0 && ix < W ? src[((int64_t)iy * W + ix) * C + c] : 0.f;
-          acc = __builtin_fmaf(x, wm[t * Cg + c], acc);
-        }
-      dst[((int64_t)oy * W + ox) * M + mw + m] = raw ? acc : fmaxf(acc + bias[mw + m], 0.f);
-    }
-    return;
-  }
-
   // Epilogue: each wave stages its 64 pixels x 64 channels (256-byte rows, 16-byte chunks swizzled by
   // the pixel) and writes whole rows, 16 lanes per pixel.
   float* stg = (float*)s_mem + wn * (64 * 64);
@@ -1124,6 +1167,7 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
   using hfrag = Op::half_frag;
   typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
   constexpr int TM = P::TM, TN = P::TN;
+  const bool exact = *special;  // no split at all
   __shared__ __align__(1024) __bf16 s_mem[P::LDS_E];
 
   const int nb = gridDim.x, xcd = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
@@ -1275,31 +1319,60 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
       });
     }
   };
-  switch (tnv) {
+  if (!exact) switch (tnv) {
     case 2: channels(std::integral_constant<int, 2>{}); break;
     case 1: channels(std::integral_constant<int, 1>{}); break;
     default: channels(std::integral_constant<int, 0>{}); break;
   }
 
-  const bool raw = ksplit > 1;
-  float* dst = (raw ? part + copy * part_slice : out) + rn.out_off + plane * rn.out_stride;
-  if (__syncthreads_or(top >= SPLIT_LIMIT) || *special) {
-    // Some value does not split: this workgroup's outputs in fp32, one pixel per thread.
-    const int oy = oy0 + tid / 16, ox = ox0 + tid % 16;
-    if (oy >= Ho || ox >= Wo) return;
-    for (int m = 0; m < 96; ++m) {
-      float a = 0.f;
-      for (int c = c_lo; c < c_hi; ++c)
-        for (int k = 0; k < K1; ++k) {
-          const int ky = conv1_ky(k), kx = conv1_kx(k);
-          if (ky < 11 && kx < 11)
-            a = __builtin_fmaf(src[((int64_t)c * H + 4 * oy + ky) * pitch + 4 * ox + kx], w[(m * 3 + c) * K1 + k], a);
+  if (__syncthreads_or(top >= SPLIT_LIMIT) || exact) {
+    // Some value does not split: this workgroup's sums on the fp32 matrix cores, as conv_f32_kernel's.  The
+    // zero-weight taps take zeros, whatever the plane holds there.
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    float* s_halo = (float*)s_mem;
+    constexpr int HSF = 76;  // floats per halo row
+    static_assert(P::HR * HSF * 2 <= P::LDS_E, "the fp32 halo fits the stage buffers");
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+      for (int t = 0; t < TN; ++t) acc[a][t] = f32x16{};
+    for (int c = c_lo; c < c_hi; ++c) {
+      __syncthreads();
+      for (int e = tid; e < P::HR * P::HR; e += P::NT) {
+        const int r = e / P::HR, x = e % P::HR;
+        s_halo[r * HSF + x] = iy0 + r < H && ix0 + x < W ? src[((int64_t)c * H + iy0 + r) * pitch + ix0 + x] : 0.f;
+      }
+      __syncthreads();
+#pragma unroll 3
+      for (int k = 0; k < P::NK; ++k) {  // rows 4 (k / 3) .. + 3, columns 4 (k % 3) .. + 3
+        v4 xv[TN][2], wv[TM][2];
+#pragma unroll
+        for (int t = 0; t < TN; ++t) {
+          const int idx = gtile(t) * 32 + l32;
+          const float* q = s_halo + (4 * (idx / 16) + 4 * (k / 3) + 2 * half) * HSF + 4 * (idx % 16) + 4 * (k % 3);
+          xv[t][0] = *(const v4*)q, xv[t][1] = *(const v4*)(q + HSF);
+          if (k % 3 == 2) xv[t][0][3] = 0.f, xv[t][1][3] = 0.f;
+          if (k / 3 == 2 && half) xv[t][1] = v4{};
         }
-      dst[((int64_t)oy * Wo + ox) * 96 + m] = raw ? a : fmaxf(a + bias[m], 0.f);
+#pragma unroll
+        for (int mt = 0; mt < TM; ++mt) {
+          const float* q = w + ((mt * 32 + l32) * 3 + c) * K1 + 16 * k + 8 * half;
+          wv[mt][0] = *(const v4*)q, wv[mt][1] = *(const v4*)(q + 4);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+          for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+              acc[mt][t] = mma_f32(wv[mt][i >> 2][i & 3], xv[t][i >> 2][i & 3], acc[mt][t]);
+      }
     }
-    return;
+    __syncthreads();
   }
 
+  const bool raw = ksplit > 1;
+  float* dst = (raw ? part + copy * part_slice : out) + rn.out_off + plane * rn.out_stride;
   // Epilogue: per MFMA pixel tile each wave stages 32 pixels x 96 channels (384-byte rows, 16-byte chunks
   // swizzled by the pixel) and writes whole rows, 24 lanes per pixel.
   float* stg = (float*)s_mem + wv * (32 * 96);
@@ -1748,9 +1821,9 @@ int run_conv_f32(const float* in, float* out, const float* wp, const __bf16* wsp
   });
   if (blocks <= 0) return (int)hipErrorInvalidValue;
   // a tile's halo rows are addressed with 32-bit byte offsets (maps up to 77,000 columns wide)
-  int scalar = 0;
+  int wide = 0;
   for (int i = 0; i < n_runs; ++i)
-    if ((int64_t)Cf::HH * runs[i].W * C * (int64_t)sizeof(float) >= 0x7fffffffLL) scalar = 1;
+    if ((int64_t)Cf::HH * runs[i].W * C * (int64_t)sizeof(float) >= 0x7fffffffLL) wide = 1;
   int ks = split_copies(blocks, Cg / 16);
   const int64_t span = split_span(runs, n_runs);  // elements of one partial copy
   const size_t need = ks > 1 ? (size_t)ks * (size_t)span * sizeof(float) : 0;
@@ -1761,7 +1834,7 @@ int run_conv_f32(const float* in, float* out, const float* wp, const __bf16* wsp
   if (ks > 1 && (!part || part_bytes < need)) ks = 1;
   if (blocks * ks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
 #define DN_F32_ARGS in, out, wsplit, wp, special, bias, kr, C, Cg, M, Mg, mblocks, ks, (int)blocks, part, span, \
-                    scalar
+                    wide
   if (n_runs == 1)
     conv_f32_kernel<R, false><<<(unsigned)(blocks * ks), P::NT, 0, s>>>(DN_F32_ARGS);
   else

@@ -383,3 +383,56 @@ def test_conv_pixel_sequences(D, layer, n, H, W):
                                          b.double(), s, p, 1, G).clamp(min=0).permute(0, 2, 3, 1)[0]
         # half an ulp of bf16 (2^-9 relative to the value's binade: 2^-8 of the value) and fp32 sums
         assert bool(((out[i].double().cpu() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-3).all())
+
+
+# Tile edges, partial tiles in both layouts, several chunks and groups, rows of odd length in conv1.
+@pytest.mark.parametrize("layer,shape", [(1, (1, 11, 11)), (1, (2, 75, 140)), (1, (1, 139, 77)), (2, (1, 1, 1)),
+                                         (2, (2, 17, 33)), (3, (2, 16, 16)), (3, (1, 33, 5)), (4, (2, 5, 35)),
+                                         (5, (1, 18, 40))])
+def test_f32_conv_fallback(D, layer, shape):
+    """One weight that does not split sends every workgroup to the fp32 matrix cores; its input channel is
+    zero, so that it adds nothing.  Products of fp32 values are exact there and a sum of K terms is
+    rounded at most K + 1 times, each by half an ulp of a partial sum no larger than S: (K + 1) 2^-24 S."""
+    M, C, R, _, _, G = LAYERS[layer - 1]
+    n, H, W = shape
+    g = torch.Generator().manual_seed(H * 37 + W + layer)
+    w = torch.randn((M, C // G, R, R), generator=g) * 0.05
+    b = torch.randn(M, generator=g)
+    x = torch.randn((n, 3, H, W) if layer == 1 else (n, H, W, C), generator=g) * 40
+    (x[:, 1] if layer == 1 else x[..., 1::C // G]).zero_()
+    w[M - 2, 1, R - 1, 0] = 3.4e38
+    out, ref = f32_layer(D, layer, x, (w, b))
+    w[M - 2, 1, R - 1, 0] = 0
+    _, total = f32_layer(D, layer, x.abs(), (w.abs(), b.abs()))
+    K = C // G * R * R
+    assert bool(((out - ref).abs() <= (K + 1) * 2.0 ** -24 * total).all())
+    assert float((out - ref).norm() / ref.norm()) <= 2e-6
+
+
+@pytest.mark.parametrize("layer", [1, 2, 3, 4, 5])
+def test_f32_conv_fallback_in_split_launches(D, layer):
+    """The same inside the whole stack on planes of two sizes (launches of several runs that split their
+    input channels): the input channel that the weight reads is zero (a channel of the plane, or an
+    output channel of the layer before with no weights), so the maps equal those without the weight to
+    the stack's fp32 rounding."""
+    rng = torch.Generator().manual_seed(layer)
+    ws = [[torch.from_numpy(w).clone(), torch.from_numpy(b).clone()] for w, b in W7]
+    planes = torch.randn(3 * (227 * 227 + 195 * 211), generator=rng) * 50
+    descs = []
+    for h, w, off in ((227, 227, 0), (195, 211, 3 * 227 * 227)):
+        d = D.dn_plane_desc()
+        d.h, d.w, d.offset = h, w, off
+        descs.append(d)
+        if layer == 1:
+            planes[off + h * w:off + 2 * h * w] = 0
+    if layer > 1:
+        ws[layer - 2][0][1] = 0
+        ws[layer - 2][1][1] = -1
+    maps = []
+    for value in (0.0, 3.4e38):
+        ws[layer - 1][0][2, 1, 0, 0] = value
+        pk = D.densenet_pack_weights([(w.cuda(), b.cuda()) for w, b in ws], DTS["f32"])
+        cf = D.densenet_conv_features(planes.cuda(), descs, DTS["f32"], pk, D.net_params())
+        maps.append([m.double().cpu() for m in cf.conv5_maps()])
+    for a, b in zip(*maps):
+        assert float((a - b).norm() / a.norm()) <= 4e-6
