@@ -901,7 +901,7 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
     const int e = tid + i * P::NT, v = e & 3, p = e >> 2;
     const int iy = oy0 - pad + p / Cf::HW, ix = ox0 - pad + p % Cf::HW;
     const bool ok = e < P::HALO_V && iy >= 0 && iy < H && ix >= 0 && ix < W;
-    hoff[i] = ok ? (uint32_t)((((iy - iy_first) * W + ix) * C + 4 * v) * (int)sizeof(float)) : OOB;
+    hoff[i] = ok ? (((uint32_t)(iy - iy_first) * (uint32_t)W + (uint32_t)ix) * (uint32_t)C + 4u * v) * 4u : OOB;
   }
   u32x4_t hreg[P::HALO_PER];
   auto load_halo = [&](int chunk) {
@@ -1152,7 +1152,7 @@ struct Split1 {
 };
 
 // wsplit: per input channel and k-step [3][96][2 slots] of bf16, in LDS order; w: [96][3][144] fp32.
-// ksplit > 1: as conv_f32_kernel's split, over the three input channels.
+// ksplit > 1: as conv_f32_kernel's split, over the three input channels; wide: as conv_f32_kernel's.
 template <bool MULTI>
 __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restrict__ in, float* __restrict__ out,
                                                            const __bf16* __restrict__ wsplit,
@@ -1160,14 +1160,14 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
                                                            const uint32_t* __restrict__ special,
                                                            const float* __restrict__ bias, KRuns runs, int ksplit,
                                                            int base, float* __restrict__ part,
-                                                           int64_t part_slice) {
+                                                           int64_t part_slice, int wide) {
   using P = Split1;
   using Op = Mfma<__bf16>;
   using frag = Op::frag;
   using hfrag = Op::half_frag;
   typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
   constexpr int TM = P::TM, TN = P::TN;
-  const bool exact = *special;  // no split at all
+  const bool exact = *special || wide;  // no split at all
   __shared__ __align__(1024) __bf16 s_mem[P::LDS_E];
 
   const int nb = gridDim.x, xcd = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
@@ -1189,13 +1189,13 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
   constexpr uint32_t OOB = 0x80000000u;
 
   // Halo loads: four pixels of a row each, at byte offsets from the tile's first row (the rows of one
-  // channel; 16-byte loads at 4-byte alignment).  Columns from W on are replaced by zeros.
+  // channel, less than 2^31 bytes, or `wide` is set; 16-byte loads at 4-byte alignment).  Columns from W on are replaced by zeros.
   const int rows = min(P::HR, H - iy0);
   uint32_t hoff[P::HALO_PER];
 #pragma unroll
   for (int i = 0; i < P::HALO_PER; ++i) {
     const int e = tid + i * P::NT, r = e / 18, x = ix0 + 4 * (e % 18);
-    hoff[i] = e < P::HALO_V && r < rows && x < W ? (uint32_t)((r * pitch + x) * (int)sizeof(float)) : OOB;
+    hoff[i] = e < P::HALO_V && r < rows && x < W ? ((uint32_t)r * (uint32_t)pitch + (uint32_t)x) * 4u : OOB;
   }
   u32x4_t hreg[P::HALO_PER];
   auto load_halo = [&](int c) {
@@ -2041,12 +2041,16 @@ int conv_dispatch(int layer, const void* d_in, const MapRun* runs, int n_runs, c
       if (ks > 1 && (!part || part_bytes < need)) ks = 1;
       const __bf16* wsplit = (const __bf16*)ws;
       const uint32_t* special = (const uint32_t*)((const char*)d_packed + L.special_off);
+      // a tile's halo rows are addressed with 32-bit byte offsets (rows up to 7.4 million values apart)
+      int wide = 0;
+      for (int i = 0; i < n_runs; ++i)
+        if ((int64_t)Split1::HR * std::max(runs[i].pitch, runs[i].W) * (int64_t)sizeof(float) >= 0x7fffffffLL) wide = 1;
       if (n_runs == 1)
         conv1_f32_kernel<false><<<(unsigned)(blocks * ks), 256, 0, s>>>(in, out, wsplit, wp, special, bias, kr, ks,
-                                                                         (int)blocks, part, span);
+                                                                         (int)blocks, part, span, wide);
       else
         conv1_f32_kernel<true><<<(unsigned)(blocks * ks), 256, 0, s>>>(in, out, wsplit, wp, special, bias, kr, ks,
-                                                                        (int)blocks, part, span);
+                                                                        (int)blocks, part, span, wide);
       if (ks > 1) {
         KRuns rr;
         const int64_t rb = fill_kruns(runs, n_runs, rr, [](KRun& k) {

@@ -436,3 +436,38 @@ def test_f32_conv_fallback_in_split_launches(D, layer):
         maps.append([m.double().cpu() for m in cf.conv5_maps()])
     for a, b in zip(*maps):
         assert float((a - b).norm() / a.norm()) <= 4e-6
+
+
+# rows 2^31 / 72 bytes apart and more (below: split parts; then 64-bit addresses), and 2^32 / 72
+@pytest.mark.parametrize("pitch", [7_400_000, 7_500_032, 15_000_064])
+def test_conv1_f32_rows_far_apart(D, pitch):
+    """fp32 planes whose tiles span more bytes than 32 bits count (up to 15 GB, of which only the plane's
+    columns are written and read) equal the same planes with packed rows, to the stack's fp32 rounding."""
+    h, w = 83, 99
+    g = torch.Generator().manual_seed(5)
+    x = torch.randn((3, h, w), generator=g) * 50
+    maps = []
+    for p in (w, pitch):
+        planes = torch.empty((3, h, p), device="cuda")
+        planes[..., :w] = x.cuda()
+        d = D.dn_plane_desc()
+        d.h, d.w, d.pitch, d.offset = h, w, p, 0
+        cf = D.densenet_conv_features(planes.view(-1), [d], DTS["f32"], packed(D, "f32"), D.net_params())
+        maps.append(cf.conv5.double().cpu())
+        del planes
+    assert float(maps[0].norm()) > 0
+    assert float((maps[0] - maps[1]).norm() / maps[0].norm()) <= 4e-6
+
+
+@pytest.mark.parametrize("layer,W", [(2, 290_000), (5, 78_000)])
+def test_conv_f32_wide_maps(D, layer, W):
+    """Maps whose tiles span more than 2^31 bytes: both ends equal the same columns of a narrow map, whose
+    last column lacks its right neighbours, to fp32 rounding (the two sum in different orders)."""
+    C = LAYERS[layer - 1][1]
+    x = torch.randn((1, 3, W, C), generator=torch.Generator("cuda").manual_seed(W), device="cuda") * 20
+    out = D.densenet_conv_layer(layer, x, 1, 3, W, DTS["f32"], packed(D, "f32"))
+    for a, b, lo, hi in ((0, 100, 0, 98), (W - 100, W, 2, 100)):
+        part = x[:, :, a:b].contiguous()
+        ref = D.densenet_conv_layer(layer, part, 1, 3, 100, DTS["f32"], packed(D, "f32"))[:, :, lo:hi].double()
+        got = out[:, :, a + lo:a + hi].double()
+        assert float((got - ref).norm() / ref.norm()) <= 2e-6
