@@ -809,7 +809,8 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * WN, OCC) void conv_flat_ker
 // accumulators of their own, so the sum of the large terms is rounded once per 16 k (the fp32 MFMA
 // rounds it once per 2 k).
 // Values that do not split (infinities, NaN, and finite values that round to a bf16 infinity) are seen
-// as they are staged (inputs) or packed (weights); a workgroup that meets one computes its sums
+// as they are staged (inputs) or packed (weights), and products that pass fp32's range in the sums (there the
+// products of the parts are infinities of both signs); a workgroup that meets one computes its sums
 // from the fp32 data with fp32 MFMAs instead (after its split sums; at once where a weight is the cause).  An
 // infinite weight: conv3 on 8 maps of 37 x 49 524 us, conv2 on 8 of 59 x 79 282, conv1 on 8 planes of 480 x 640
 // 199, against 164, 128 and 88 us where all values split, and 51, 47 and 12 ms with one thread per pixel.
@@ -1037,8 +1038,15 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
     default: chunks(std::integral_constant<int, 0>{}); break;
   }
 
-  if (__syncthreads_or(top >= SPLIT_LIMIT) || exact) {
-    // Some value does not split: this workgroup's sums on the fp32 matrix cores (32x32x2), from the fp32
+  f32x4 fin = f32x4{};  // 0 while every sum is finite, else NaN; four chains
+#pragma unroll
+  for (int mt = 0; mt < TM; ++mt)
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) fin[e & 3] = __builtin_fmaf(big[mt][t][e] + small[mt][t][e], 0.f, fin[e & 3]);
+  if (__syncthreads_or(top >= SPLIT_LIMIT || fin[0] + fin[1] + fin[2] + fin[3] != 0.f) || exact) {
+    // Some value or sum does not split: this workgroup's sums on the fp32 matrix cores (32x32x2), from the fp32
     // data with 64-bit addresses.  Per chunk the halo is staged as floats; each lane takes 8 channels of
     // its pixel (LDS) and of its output channel (weights, from L2), one per MFMA.
     typedef float v4 __attribute__((ext_vector_type(4)));
@@ -1325,8 +1333,15 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
     default: channels(std::integral_constant<int, 0>{}); break;
   }
 
-  if (__syncthreads_or(top >= SPLIT_LIMIT) || exact) {
-    // Some value does not split: this workgroup's sums on the fp32 matrix cores, as conv_f32_kernel's.  The
+  f32x4 fin = f32x4{};  // 0 while every sum is finite, else NaN; four chains
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int t = 0; t < TN; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) fin[e & 3] = __builtin_fmaf(acc[a][t][e], 0.f, fin[e & 3]);
+  if (__syncthreads_or(top >= SPLIT_LIMIT || fin[0] + fin[1] + fin[2] + fin[3] != 0.f) || exact) {
+    // Some value or sum does not split: this workgroup's sums on the fp32 matrix cores, as conv_f32_kernel's.  The
     // zero-weight taps take zeros, whatever the plane holds there.
     typedef float v4 __attribute__((ext_vector_type(4)));
     float* s_halo = (float*)s_mem;

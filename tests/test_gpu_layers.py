@@ -471,3 +471,34 @@ def test_conv_f32_wide_maps(D, layer, W):
         ref = D.densenet_conv_layer(layer, part, 1, 3, 100, DTS["f32"], packed(D, "f32"))[:, :, lo:hi].double()
         got = out[:, :, a + lo:a + hi].double()
         assert float((got - ref).norm() / ref.norm()) <= 2e-6
+
+
+@pytest.mark.parametrize("layer", [1, 2, 3])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_f32_split_conv_products_that_overflow(D, layer, sign):
+    """Inputs and weights around 1e21 split, but their products pass fp32's range, and the products of
+    their parts have both signs: the outputs they reach are an infinity (0 after ReLU when it is negative),
+    the others what they are without.  Each output has one such product (weights of input channel 1 at
+    one tap, on input pixels 1 of 4 in either direction)."""
+    M, C, R, s, p, G = LAYERS[layer - 1]
+    n, H, W = (1, 91, 87) if layer == 1 else (1, 19, 21)
+    g = torch.Generator().manual_seed(layer)
+    w = torch.rand((M, C // G, R, R), generator=g) * 0.5 + 0.25
+    w *= 1 - 2 * torch.randint(0, 2, w.shape, generator=g)
+    x = torch.rand((n, 3, H, W) if layer == 1 else (n, H, W, C), generator=g) * 0.5 + 0.25
+    w[3:19, 1, R // 2, R // 2] = sign * 1e21 * (1 + torch.rand(16, generator=g))
+    plane = x[0, 1] if layer == 1 else x[0, :, :, 1]
+    at = plane[4 * 9 + 1::16, 4 * 9 + 1::16] if layer == 1 else plane[1::4, 1::4]
+    at.copy_(1e21 * (1 + torch.rand(at.shape, generator=g)))
+    out, ref = f32_layer(D, layer, x, (w, torch.zeros(M)))
+    over = ref.abs() > 3.5e38
+    if sign < 0:                      # what overflows to -inf is 0 after ReLU, in fp64 too: find it by its inputs
+        over = f32_layer(D, layer, x, (-w, torch.zeros(M)))[1] > 3.5e38
+    assert int(over.sum()) >= 16
+    assert bool((out[over] == (float("inf") if sign > 0 else 0.0)).all())
+    rest = ~over
+    assert bool(torch.isfinite(out[rest]).all())
+    # a finite output holds up to 4 products of about 1e21 and may be their difference
+    assert bool(((out - ref)[rest].abs() <= 1e-6 * (ref[rest] + 8e21)).all())
+    ok = rest & (ref < 1e6)
+    assert float((out - ref)[ok].norm() / ref[ok].norm()) <= 1e-6
