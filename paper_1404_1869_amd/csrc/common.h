@@ -113,7 +113,7 @@ int launch_warp_regions(const uint8_t* d_img, int32_t n_img, int32_t H, int32_t 
 // Packed weight blob: offsets in bytes of each layer's weights and fp32 biases, and of a second,
 // stage-major copy of the weights that the direct-load conv kernels stream as contiguous blocks (0 when
 // absent; fp32: three bf16 parts of each weight).  special_off (fp32): a word per layer, non-zero when a
-// weight has no such parts (an infinity, a NaN or a value beyond bf16's range).
+// weight has no such parts (an infinity, a NaN or a magnitude from 5.2e33).
 struct PackedLayout {
   size_t w_off[5], b_off[5], s_off[5], special_off, total;
 };

@@ -115,10 +115,15 @@ __global__ void pack_stage_kernel(const float* __restrict__ w, T* __restrict__ o
   out[i] = from_f32<T>(w[((oc * Cg + c) * R + ky) * R + kx]);
 }
 
-// Bits of |x| from which x rounds to a bf16 infinity (or is one, or a NaN).
+// Values are split times 2^16: fp32's smallest step, 2^-149, is then 2^-133, bf16's smallest (the matrix
+// cores keep bf16's subnormals), so the parts hold every fp32 value below the limit exactly.  Unscaled, the
+// third part runs out of bf16's range below 2^-110 (1e-34 is off by 2e-7 of it, 1e-36 by 2e-5, 1.3e-38 by
+// 2e-3).  UNSPLIT takes a sum of products back.
+constexpr float SPLIT_SCALE = 0x1p16f, UNSPLIT = 0x1p-32f;
+// Bits of |2^16 x| from which it rounds to a bf16 infinity (|x| from 5.2e33, infinities, NaN).
 constexpr uint32_t SPLIT_LIMIT = 0x7f7f8000u;
 
-// x = h + m + l, each the nearest bf16 of the rest.
+// x (scaled) = h + m + l, each the nearest bf16 of the rest.
 struct Split3 {
   __bf16 h, m, l;
 };
@@ -144,7 +149,7 @@ __global__ void pack_split_kernel(const float* __restrict__ w, __bf16* __restric
   const int tap = (int)(r % RR), nchunks = Cg / 16, chunk = (int)((r / RR) % nchunks);
   const int64_t blk = r / RR / nchunks;
   const int64_t oc = blk * 64 + m;  // blocks run through the groups' channels in order
-  const float x = w[(oc * Cg + chunk * 16 + c) * RR + tap];
+  const float x = SPLIT_SCALE * w[(oc * Cg + chunk * 16 + c) * RR + tap];
   if ((__builtin_bit_cast(uint32_t, x) & 0x7fffffffu) >= SPLIT_LIMIT) atomicOr(special, 1u);
   const Split3 s = split3(x);
   __bf16* d = out + r * (3 * 64 * 16) + m * 16 + ((c >> 3) ^ ((m >> 4) & 1)) * 8 + (c & 7);
@@ -161,7 +166,7 @@ __global__ void pack_split1_kernel(const float* __restrict__ w, __bf16* __restri
   if (i >= 3 * K1 * 96) return;
   const int kk = i % 16, m = (i / 16) % 96, cs = i / (16 * 96);  // cs = channel * 9 + k-step
   const int c = cs / (K1 / 16), k = (cs % (K1 / 16)) * 16 + kk, ky = conv1_ky(k), kx = conv1_kx(k);
-  const float x = ky < 11 && kx < 11 ? w[((m * 3 + c) * 11 + ky) * 11 + kx] : 0.f;
+  const float x = ky < 11 && kx < 11 ? SPLIT_SCALE * w[((m * 3 + c) * 11 + ky) * 11 + kx] : 0.f;
   if ((__builtin_bit_cast(uint32_t, x) & 0x7fffffffu) >= SPLIT_LIMIT) atomicOr(special, 1u);
   const Split3 s = split3(x);
   __bf16* d = out + cs * (3 * 96 * 16) + m * 16 + ((kk >> 3) ^ ((m >> 4) & 1)) * 8 + (kk & 7);
@@ -808,9 +813,9 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * WN, OCC) void conv_flat_ker
 // of the same k, and run at 16 times their rate.  h h' and the five small terms are summed in
 // accumulators of their own, so the sum of the large terms is rounded once per 16 k (the fp32 MFMA
 // rounds it once per 2 k).
-// Values that do not split (infinities, NaN, and finite values that round to a bf16 infinity) are seen
+// Values that do not split (infinities, NaN, and finite values from 5.2e33) are seen
 // as they are staged (inputs) or packed (weights), and products that pass fp32's range in the sums (there the
-// products of the parts are infinities of both signs); a workgroup that meets one computes its sums
+// products of the parts are infinities of both signs; as sums are 2^32 times too large, from 7.9e28); a workgroup that meets one computes its sums
 // from the fp32 data with fp32 MFMAs instead (after its split sums; at once where a weight is the cause).  An
 // infinite weight: conv3 on 8 maps of 37 x 49 524 us, conv2 on 8 of 59 x 79 282, conv1 on 8 planes of 480 x 640
 // 199, against 164, 128 and 88 us where all values split, and 51, 47 and 12 ms with one thread per pixel.
@@ -827,6 +832,17 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * WN, OCC) void conv_flat_ker
 // One fp32 MFMA: two k, offset lane / 32; the accumulator's layout is the 16-bit tile's.
 __device__ inline f32x16 mma_f32(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// The larger of m and every |v|; NaN when any is NaN (two values per v_maximum3_f32).
+__device__ inline float max_or_nan(float m, const f32x16& v) {
+  float a = m, b = 0.f;
+#pragma unroll
+  for (int e = 0; e < 16; e += 4) {
+    a = __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, __builtin_fabsf(v[e])), __builtin_fabsf(v[e + 1]));
+    b = __builtin_elementwise_maximum(__builtin_elementwise_maximum(b, __builtin_fabsf(v[e + 2])), __builtin_fabsf(v[e + 3]));
+  }
+  return __builtin_elementwise_maximum(a, b);
 }
 
 template <int R>
@@ -910,7 +926,18 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
     for (int i = 0; i < P::HALO_PER; ++i)
       hreg[i] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc_in, hoff[i], chunk * 64, 0));
   };
-  uint32_t top = 0;  // largest |x| staged, as bits
+  // Scales the loaded values; called where MFMAs are in flight.
+  uint32_t top = 0;  // largest |2^16 x|, as bits
+  auto scale_halo = [&] {
+#pragma unroll
+    for (int i = 0; i < P::HALO_PER; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t bits = __builtin_bit_cast(uint32_t, SPLIT_SCALE * __builtin_bit_cast(float, (uint32_t)hreg[i][q]));
+        hreg[i][q] = bits;
+        top = max(top, bits & 0x7fffffffu);
+      }
+  };
   auto store_halo = [&] {
     typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
 #pragma unroll
@@ -920,10 +947,8 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
         bf4 h, m, l;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const uint32_t bits = hreg[i][q];
-          const Split3 sp = split3(__builtin_bit_cast(float, bits));
+          const Split3 sp = split3(__builtin_bit_cast(float, (uint32_t)hreg[i][q]));
           h[q] = sp.h, m[q] = sp.m, l[q] = sp.l;
-          top = max(top, bits & 0x7fffffffu);
         }
         __bf16* d = s_mem + Cf::halo_off(p / Cf::HW, p % Cf::HW, v >> 1) + 4 * (v & 1);
         *(bf4*)d = h;
@@ -978,6 +1003,7 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
     constexpr int TNV = decltype(tnv_c)::value;
     load_halo(c_lo);
     load_w(0, c_lo, std::integral_constant<int, 0>{});
+    scale_halo();
     store_halo();
     wait_vmem();
     __syncthreads();
@@ -991,6 +1017,7 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
           load_w(buf ^ 1, chunk, std::integral_constant<int, S + 1>{});
         else if (next)
           load_w(buf ^ 1, chunk + 1, std::integral_constant<int, 0>{});
+        if (S + 1 == P::NS && next) scale_halo();  // loaded by the first stage's end
         if constexpr (TNV > 0) {
           const __bf16* ws = s_mem + P::W_OFF + buf * (P::TS * P::TAP_E);
           static_for<P::TS * S, (P::TS * (S + 1) < RR ? P::TS * (S + 1) : RR)>([&](auto tc) {
@@ -1038,14 +1065,18 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
     default: chunks(std::integral_constant<int, 0>{}); break;
   }
 
-  f32x4 fin = f32x4{};  // 0 while every sum is finite, else NaN; four chains
+  float peak = 0.f;  // largest |sum|, or NaN
 #pragma unroll
   for (int mt = 0; mt < TM; ++mt)
 #pragma unroll
-    for (int t = 0; t < TN; ++t)
+    for (int t = 0; t < TN; ++t) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) fin[e & 3] = __builtin_fmaf(big[mt][t][e] + small[mt][t][e], 0.f, fin[e & 3]);
-  if (__syncthreads_or(top >= SPLIT_LIMIT || fin[0] + fin[1] + fin[2] + fin[3] != 0.f) || exact) {
+      for (int e = 0; e < 16; ++e) big[mt][t][e] += small[mt][t][e];
+      peak = max_or_nan(peak, big[mt][t]);
+    }
+  float unsplit = UNSPLIT;
+  if (__syncthreads_or(top >= SPLIT_LIMIT || !(peak < INFINITY)) || exact) {
+    unsplit = 1.f;
     // Some value or sum does not split: this workgroup's sums on the fp32 matrix cores (32x32x2), from the fp32
     // data with 64-bit addresses.  Per chunk the halo is staged as floats; each lane takes 8 channels of
     // its pixel (LDS) and of its output channel (weights, from L2), one per MFMA.
@@ -1056,7 +1087,7 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
 #pragma unroll
     for (int mt = 0; mt < TM; ++mt)
 #pragma unroll
-      for (int t = 0; t < TN; ++t) big[mt][t] = f32x16{}, small[mt][t] = f32x16{};
+      for (int t = 0; t < TN; ++t) big[mt][t] = f32x16{};
     const float* wl = w + (int64_t)(g * Mg + m0 + l32) * RR * Cg + 8 * half;
     for (int c0 = 16 * c_lo; c0 < 16 * c_hi; c0 += 16) {
       __syncthreads();
@@ -1113,7 +1144,7 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
         const int p = t * 32 + l32, j = 8 * mt + 2 * q + half;
         f32x4 r;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = big[mt][t][4 * q + e] + small[mt][t][4 * q + e];
+        for (int e = 0; e < 4; ++e) r[e] = big[mt][t][4 * q + e] * unsplit;
         *(f32x4*)(stg + p * 64 + ((j ^ (p & 15)) * 4)) = r;
       }
   wave_lds_order();
@@ -1213,7 +1244,21 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
     for (int i = 0; i < P::HALO_PER; ++i)
       hreg[i] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, hoff[i], 0, 0));
   };
-  uint32_t top = 0;  // largest |x| staged, as bits
+  // Scales the loaded values and drops those past the row; called where MFMAs are in flight.
+  uint32_t top = 0;  // largest |2^16 x|, as bits
+  auto scale_halo = [&] {
+#pragma unroll
+    for (int i = 0; i < P::HALO_PER; ++i) {
+      const int x = ix0 + 4 * ((tid + i * P::NT) % 18);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float v = SPLIT_SCALE * __builtin_bit_cast(float, (uint32_t)hreg[i][q]);
+        const uint32_t bits = x + q < W ? __builtin_bit_cast(uint32_t, v) : 0u;
+        hreg[i][q] = bits;
+        top = max(top, bits & 0x7fffffffu);
+      }
+    }
+  };
   auto store_halo = [&] {
     typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
 #pragma unroll
@@ -1223,11 +1268,8 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
         bf4 h, m, l;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          uint32_t bits = hreg[i][q];
-          if (ix0 + xc + q >= W) bits = 0u;
-          const Split3 sp = split3(__builtin_bit_cast(float, bits));
+          const Split3 sp = split3(__builtin_bit_cast(float, (uint32_t)hreg[i][q]));
           h[q] = sp.h, m[q] = sp.m, l[q] = sp.l;
-          top = max(top, bits & 0x7fffffffu);
         }
         __bf16* d = s_mem + r * P::HS + xc;
         *(bf4*)d = h;
@@ -1270,6 +1312,7 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
     constexpr int TNV = decltype(tnv_c)::value;
     load_halo(c_lo);
     load_w(0, c_lo, std::integral_constant<int, 0>{});
+    scale_halo();
     store_halo();
     wait_vmem();
     __syncthreads();
@@ -1283,6 +1326,7 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
           load_w(buf ^ 1, c, std::integral_constant<int, S + 1>{});
         else if (next)
           load_w(buf ^ 1, c + 1, std::integral_constant<int, 0>{});
+        if (S + 1 == P::NS && next) scale_halo();  // loaded by the first stage's end
         if constexpr (TNV > 0) {
           const __bf16* ws = s_mem + P::W_OFF + buf * (P::TS * P::KSE);
           static_for<P::TS * S, (P::TS * (S + 1) < P::NK ? P::TS * (S + 1) : P::NK)>([&](auto jc) {
@@ -1333,14 +1377,14 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
     default: channels(std::integral_constant<int, 0>{}); break;
   }
 
-  f32x4 fin = f32x4{};  // 0 while every sum is finite, else NaN; four chains
+  float peak = 0.f;  // largest |sum|, or NaN
 #pragma unroll
   for (int a = 0; a < TM; ++a)
 #pragma unroll
-    for (int t = 0; t < TN; ++t)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) fin[e & 3] = __builtin_fmaf(acc[a][t][e], 0.f, fin[e & 3]);
-  if (__syncthreads_or(top >= SPLIT_LIMIT || fin[0] + fin[1] + fin[2] + fin[3] != 0.f) || exact) {
+    for (int t = 0; t < TN; ++t) peak = max_or_nan(peak, acc[a][t]);
+  float unsplit = UNSPLIT;
+  if (__syncthreads_or(top >= SPLIT_LIMIT || !(peak < INFINITY)) || exact) {
+    unsplit = 1.f;
     // Some value or sum does not split: this workgroup's sums on the fp32 matrix cores, as conv_f32_kernel's.  The
     // zero-weight taps take zeros, whatever the plane holds there.
     typedef float v4 __attribute__((ext_vector_type(4)));
@@ -1401,7 +1445,7 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
         const int j = 8 * mt + 2 * q + half;
         f32x4 r;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = acc[mt][t][4 * q + e];
+        for (int e = 0; e < 4; ++e) r[e] = acc[mt][t][4 * q + e] * unsplit;
         *(f32x4*)(stg + l32 * 96 + ((j ^ ((l32 >> 2) & 7)) * 4)) = r;
       }
     wave_lds_order();

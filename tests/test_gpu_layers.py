@@ -502,3 +502,23 @@ def test_f32_split_conv_products_that_overflow(D, layer, sign):
     assert bool(((out - ref)[rest].abs() <= 1e-6 * (ref[rest] + 8e21)).all())
     ok = rest & (ref < 1e6)
     assert float((out - ref)[ok].norm() / ref[ok].norm()) <= 1e-6
+
+
+@pytest.mark.parametrize("layer", [1, 2, 3])
+@pytest.mark.parametrize("k", [-112, -118, -125, -138])
+@pytest.mark.parametrize("where", ["input", "weight"])
+def test_f32_split_conv_small_values(D, layer, k, where):
+    """Values down to fp32's subnormals (the other operand large, so that the outputs are ordinary numbers)
+    are held in full: fp64 of the same fp32 values, to test_f32_split_conv's bar and norm."""
+    M, C, R, _, _, G = LAYERS[layer - 1]
+    n, H, W = (1, 75, 83) if layer == 1 else (1, 17, 19)
+    g = torch.Generator().manual_seed(layer - k)
+    w = torch.randn((M, C // G, R, R), generator=g)
+    x = torch.randn((n, 3, H, W) if layer == 1 else (n, H, W, C), generator=g)
+    x, w = (x * 2.0 ** k, w * 2.0 ** 60) if where == "input" else (x * 2.0 ** 60, w * 2.0 ** k)
+    assert k > -126 or bool((x if where == "input" else w).abs().max() < 2.0 ** -126)
+    out, ref = f32_layer(D, layer, x, (w, torch.zeros(M)))
+    _, total = f32_layer(D, layer, x.abs(), (w.abs(), torch.zeros(M)))
+    K = C // G * R * R * (144 / 121 if layer == 1 else 1)
+    assert bool(((out - ref).abs() <= (2.0 ** -24 + (6 * K / 16 + 2) * 2.0 ** -24) * total).all())
+    assert float((out - ref).norm() / ref.norm()) <= 1e-6
