@@ -806,13 +806,15 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * WN, OCC) void conv_flat_ker
 }
 
 // ------------------------------------------------------------------------------------------------
-// Stride-1 conv for fp32 storage on the bf16 matrix cores.  An fp32 value is split into three bf16
-// values, x = h + m + l + d with |d| <= 2^-27 |x| (each the nearest bf16 of what is left), and a product
-// x w is h h' + (h m' + m h') + (m m' + h l' + l h'): the dropped terms are below 2^-25 |x w| and of
-// both signs, less than the half ulp an fp32 product is off by.  Six bf16 MFMAs replace eight fp32 ones
-// of the same k, and run at 16 times their rate.  h h' and the five small terms are summed in
+// Stride-1 conv for fp32 storage on the bf16 matrix cores, by the three-way bf16 split with six products of
+// Henry, Tang and Heinecke ("Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision
+// Computations", ARITH 2019).  A value is x = h + m + l, each the nearest bf16 of what is left: exact, with
+// |m| <= 2^-8 |x| and |l| <= 2^-17 |x|.  A product x w is taken as h h' + (h m' + m h') + (m m' + h l' + l h');
+// the dropped m l' + l m' + l l' are at most 2^-24 (1 + 2^-10) |x w| and of both signs, so one product may be off by
+// about the half ulp that rounding it to fp32 would cost (an fp32 MFMA rounds its sum only).  Six bf16 MFMAs replace eight fp32
+// ones of the same k, and run at 16 times their rate.  h h' and the five small terms are summed in
 // accumulators of their own, so the sum of the large terms is rounded once per 16 k (the fp32 MFMA
-// rounds it once per 2 k).
+// rounds it once per 2 k): over a layer's K the error against 64 bits falls two to three times.
 // Values that do not split (infinities, NaN, and finite values from 5.2e33) are seen
 // as they are staged (inputs) or packed (weights), and products that pass fp32's range in the sums (there the
 // products of the parts are infinities of both signs; as sums are 2^32 times too large, from 7.9e28); a workgroup that meets one computes its sums
@@ -825,8 +827,8 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * WN, OCC) void conv_flat_ker
 // streamed by direct loads from the split copy.  The next chunk's halo is loaded into registers while
 // a chunk computes and is split between two barriers at its end.  72 MFMAs lie between two barriers, so
 // the two workgroups of a CU (77 KB of LDS at R = 5) cover each other's waits.  Bound by the matrix cores.
-// Against fp32 MFMAs (32x32x2, one 16-bit-sized pipeline per CU): conv3 on 8 maps of 37 x 49 594 -> 176 us
-// (146 TFLOP/s of fp32 work, 0.88 PFLOP/s of bf16 products), conv2 of a 480 x 640 image's 8-scale pyramid
+// Against fp32 MFMAs (32x32x2, one 16-bit-sized pipeline per CU): conv3 on 8 maps of 37 x 49 596 -> 151 us
+// (170 TFLOP/s of fp32 work, 1.02 PFLOP/s of bf16 products), conv2 of a 480 x 640 image's 8-scale pyramid
 // 624 -> 141 us; error against 64 bits 7.1e-7 -> 2.6e-7 of the 2-norm.
 // ------------------------------------------------------------------------------------------------
 // One fp32 MFMA: two k, offset lane / 32; the accumulator's layout is the 16-bit tile's.

@@ -269,9 +269,10 @@ def f32_layer(D, layer, x, weights):
                                          (2, (1, 1, 1)), (2, (2, 17, 33)), (3, (1, 2, 2)), (3, (2, 16, 16)),
                                          (3, (1, 33, 5)), (4, (2, 5, 35)), (5, (1, 18, 40))])
 def test_f32_split_conv(D, layer, shape):
-    """fp32 layers on bf16 matrix cores: the three-part products are exact to 2^-25 of |x w| each, and
-    the sum of K terms is rounded at most 6 K / 16 + 2 times, each by half an ulp (2^-24) of a partial
-    sum no larger than S = sum |x w| + |b|: |error| <= (2^-25 + (6 K / 16 + 2) 2^-24) S."""
+    """fp32 layers on bf16 matrix cores: the six products kept of x w leave out at most d |x w|, d = 2^-24 (1 + 2^-10) (parts
+    |m| <= 2^-8 |x| and |l| <= 2^-17 |x|: m l' + l m' + l l'), and the sum of K terms is rounded at most
+    6 K / 16 + 2 times, each by half an ulp (2^-24) of a partial sum no larger than S = sum |x w| + |b|:
+    |error| <= (d + (6 K / 16 + 2) 2^-24) S."""
     M, C, R, _, _, G = LAYERS[layer - 1]
     n, H, W = shape
     g = torch.Generator().manual_seed(H * 31 + W + layer)
@@ -281,7 +282,7 @@ def test_f32_split_conv(D, layer, shape):
     out, ref = f32_layer(D, layer, x, (w, b))
     _, total = f32_layer(D, layer, x.abs(), (w.abs(), b.abs()))
     K = C // G * R * R * (144 / 121 if layer == 1 else 1)
-    bar = (2.0 ** -25 + (6 * K / 16 + 2) * 2.0 ** -24) * total
+    bar = (2.0 ** -24 * (1 + 2.0 ** -10) + (6 * K / 16 + 2) * 2.0 ** -24) * total
     assert bool(((out - ref).abs() <= bar).all())
     assert float((out - ref).norm() / ref.norm()) <= 1e-6
 
@@ -520,5 +521,5 @@ def test_f32_split_conv_small_values(D, layer, k, where):
     out, ref = f32_layer(D, layer, x, (w, torch.zeros(M)))
     _, total = f32_layer(D, layer, x.abs(), (w.abs(), torch.zeros(M)))
     K = C // G * R * R * (144 / 121 if layer == 1 else 1)
-    assert bool(((out - ref).abs() <= (2.0 ** -24 + (6 * K / 16 + 2) * 2.0 ** -24) * total).all())
+    assert bool(((out - ref).abs() <= (2.0 ** -24 * (1 + 2.0 ** -10) + (6 * K / 16 + 2) * 2.0 ** -24) * total).all())
     assert float((out - ref).norm() / ref.norm()) <= 1e-6
