@@ -595,12 +595,12 @@ __global__ __launch_bounds__(256) void pool_vector_kernel(const T* __restrict__ 
   const int H = rn.H, W = rn.W, Ho = rn.Ho, Wo = rn.Wo;
   const int plane = bid / rn.tiles_x;  // tiles_x workgroups of PPB pixels per plane
   const int tid = threadIdx.x, p = tid / G, g = tid - p * G;
-  const int q = (bid - plane * rn.tiles_x) * PPB + p;
-  const bool live = p < PPB && q < Ho * Wo;
+  const uint32_t q = (uint32_t)(bid - plane * rn.tiles_x) * PPB + p;  // output pixel of the plane, below 2^32
+  const bool live = p < PPB && q < (uint32_t)Ho * (uint32_t)Wo;
   float m[N];
   vec_t r;
   if (live) {
-    const int oy = q / Wo, ox = q - oy * Wo;
+    const int oy = (int)(q / (uint32_t)Wo), ox = (int)(q - (uint32_t)oy * (uint32_t)Wo);
     const int h = min(3, H - 2 * oy), w = min(3, W - 2 * ox);  // the clipped window
     const T* src = in + rn.in_off + plane * rn.in_stride + ((int64_t)2 * oy * W + 2 * ox) * C + g * N;
     vec_t v[3][3];
@@ -734,6 +734,9 @@ int run(const void* d_in, const MapRun* runs, int n_runs, int32_t C, bool lrn, b
       return (int64_t)q.tiles_x;
     });
     if (blocks <= 0) return (int)hipErrorInvalidValue;
+    int64_t pixels = 0;  // most output pixels of a plane
+    for (int i = 0; i < n_runs; ++i) pixels = std::max(pixels, (int64_t)kr.r[i].Ho * kr.r[i].Wo);
+    if (pixels > 0xffffff00LL) return (int)hipErrorInvalidValue;  // (64 GB of them and more)
     pool_vector_kernel<T, decltype(hn_c)::value><<<(unsigned)blocks, 256, 0, s>>>(in, out, kr, C, an, beta, k);
     return (int)hipGetLastError();
   };

@@ -523,3 +523,25 @@ def test_f32_split_conv_small_values(D, layer, k, where):
     K = C // G * R * R * (144 / 121 if layer == 1 else 1)
     assert bool(((out - ref).abs() <= (2.0 ** -24 * (1 + 2.0 ** -10) + (6 * K / 16 + 2) * 2.0 ** -24) * total).all())
     assert float((out - ref).norm() / ref.norm()) <= 1e-6
+
+
+@pytest.mark.parametrize("lrn", [False, True])
+def test_pool_more_than_2_31_output_pixels(D, lrn):
+    """One map of 92682 x 92682 pixels of 8 channels (137 GB) pools to more than 2^31 pixels: its first and
+    last rows against the same rows as maps of their own."""
+    side = 92682
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 200e9:
+        pytest.skip("needs 200 GB of free GPU memory")
+    x = torch.empty((1, side, side, 8), dtype=torch.float16, device="cuda")
+    g = torch.Generator("cuda").manual_seed(1)
+    for rows in (x[:, :3], x[:, -4:]):
+        rows.copy_(torch.randn(rows.shape, generator=g, device="cuda", dtype=torch.float16) * 30)
+    f = (lambda m: D.densenet_lrn_pool(m, DTS["f16"], D.net_params(lrn_before_pool=False))) if lrn else \
+        (lambda m: D.densenet_maxpool(m, DTS["f16"]))
+    out = f(x)
+    assert out.shape[1] * out.shape[2] > 2 ** 31
+    assert torch.equal(out[:, :1], f(x[:, :3].contiguous()))
+    assert torch.equal(out[:, -2:], f(x[:, -4:].contiguous()))
+    del x, rows, out
+    torch.cuda.empty_cache()
