@@ -110,10 +110,10 @@ int launch_warp_regions(const uint8_t* d_img, int32_t n_img, int32_t H, int32_t 
                         const int32_t* d_box_img, int32_t n, int32_t S, int32_t pitch, const float* mean,
                         dn_dtype dt, void* d_out, void* stream);
 
-// Packed weight blob: offsets in bytes of each layer's weights and fp32 biases, and of a second,
-// stage-major copy of the weights that the direct-load conv kernels stream as contiguous blocks (0 when
-// absent; fp32: three bf16 parts of each weight).  special_off (fp32): a word per layer, non-zero when a
-// weight has no such parts (an infinity, a NaN or a magnitude from 5.2e33).
+// Packed weight blob: offsets in bytes of each layer's fp32 weights (w_off; fp32 only), fp32 biases and the
+// weights in the order in which the kernels stream them (s_off; fp32: three bf16 parts of each weight).
+// special_off (fp32): a word per layer, non-zero when a weight has no such parts (an infinity, a NaN or a
+// magnitude from 5.2e33).
 struct PackedLayout {
   size_t w_off[5], b_off[5], s_off[5], special_off, total;
 };
@@ -260,8 +260,8 @@ namespace dn {
 // ---------------------------------------------------------------------------------------------
 // Device side: storage types and the gfx950 MFMA tile used by the conv kernels.
 //   32x32x16 f16 / bf16: each lane holds 8 consecutive k of row (lane % 32) of A and column
-//   (lane % 32) of B, k offset 8 * (lane / 32).  The
-//   accumulator register r of lane l holds D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
+//   (lane % 32) of B, k offset 8 * (lane / 32).  The accumulator register r of lane l holds
+//   D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
 // ---------------------------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));

@@ -24,10 +24,11 @@ namespace {
 
 // ------------------------------------------------------------------------------------------------
 // Packed weight layout
-//   conv1: [96][3][144] in dtype, k = 16 s + 8 h + 4 j + e holds tap ky = 4 (s / 3) + 2 h + j,
+//   conv1, fp32: [96][3][144], k = 16 s + 8 h + 4 j + e holds tap ky = 4 (s / 3) + 2 h + j,
 //          kx = 4 (s % 3) + e (zero where ky or kx is 11)
-//   conv2..5: [M][R*R][C/G] in dtype (tap-major, channels contiguous)
-//   conv2..5, 16-bit types, stage-major copy for conv_s1_direct_kernel: per channel block (group g,
+//   conv2..5, fp32: [M][R*R][C/G] (tap-major, channels contiguous); these copies are read where values do not split
+//   conv1, 16-bit types: see pack_conv1_resident_kernel
+//   conv2..5, 16-bit types, stage-major for conv_s1_direct_kernel and conv_flat_kernel: per channel block (group g,
 //          block of BM output channels) and stage (chunk of 16 input channels, kernel row ky), one
 //          contiguous block of R * BM * 2 16-byte pieces, piece (kx BM + m) 2 + p holding input
 //          channels 8 (p ^ ((m >> 4) & 1)) .. + 7 of the chunk at tap (ky, kx) of channel m: exactly
@@ -49,26 +50,23 @@ __host__ __device__ constexpr int conv1_kx(int k) { return 4 * ((k >> 4) % 3) + 
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-template <typename T>
-__global__ void pack_conv1_kernel(const float* __restrict__ w, T* __restrict__ out) {
+__global__ void pack_conv1_kernel(const float* __restrict__ w, float* __restrict__ out) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= 96 * 3 * K1) return;
   const int k = i % K1, mc = i / K1;  // mc = m * 3 + c
   const int ky = conv1_ky(k), kx = conv1_kx(k);
   float v = 0.f;
   if (ky < 11 && kx < 11) v = w[(mc * 11 + ky) * 11 + kx];
-  out[i] = from_f32<T>(v);
+  out[i] = v;
 }
 
-template <typename T>
-__global__ void pack_conv_kernel(const float* __restrict__ w, T* __restrict__ out, int M, int Cg,
-                                 int RR) {
+__global__ void pack_conv_kernel(const float* __restrict__ w, float* __restrict__ out, int M, int Cg, int RR) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (int64_t)M * Cg * RR) return;
   const int c = (int)(i % Cg);
   const int t = (int)((i / Cg) % RR);
   const int m = (int)(i / ((int64_t)Cg * RR));
-  out[i] = from_f32<T>(w[((int64_t)m * Cg + c) * RR + t]);
+  out[i] = w[((int64_t)m * Cg + c) * RR + t];
 }
 
 // conv1, 16-bit types, for conv1_resident_kernel: the 3 x 11 x 11 taps of an output channel as 99
@@ -307,12 +305,6 @@ struct Pieces {  // 1 KB LDS pieces, rounded up to a whole number per wave
 // Wait until every vector-memory access of this wave has completed (vmcnt 0; other counters left
 // free), as an instruction the compiler's own wait bookkeeping sees.
 __device__ inline void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-// Wait until at most N (< 16) vector-memory accesses of this wave are outstanding.
-template <int N>
-__device__ inline void wait_vmem_but() {
-  static_assert(N >= 0 && N < 16, "vmcnt field");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | N);
-}
 
 // Output stores are non-temporal: the next layer reads a batch's maps only after this launch has
 // written all of them, so they need not stay in the caches next to this layer's inputs.
@@ -2076,9 +2068,8 @@ int conv_dispatch(int layer, const void* d_in, const MapRun* runs, int n_runs, c
                   hipStream_t s) {
   const T* in = (const T*)d_in;
   T* out = (T*)d_out;
-  const T* wp = (const T*)((const char*)d_packed + L.w_off[layer - 1]);
-  // the direct-load kernels (16-bit storage) stream the stage-major copy
-  const T* ws = L.s_off[layer - 1] ? (const T*)((const char*)d_packed + L.s_off[layer - 1]) : wp;
+  const T* wp = (const T*)((const char*)d_packed + L.w_off[layer - 1]);  // fp32 only
+  const T* ws = (const T*)((const char*)d_packed + L.s_off[layer - 1]);
   const float* bias = (const float*)((const char*)d_packed + L.b_off[layer - 1]);
   if (layer == 1) {
     if (part_need) *part_need = 0;
@@ -2219,24 +2210,22 @@ int conv_dispatch(int layer, const void* d_in, const MapRun* runs, int n_runs, c
 
 PackedLayout packed_layout(dn_dtype dt) {
   PackedLayout L{};
-  const size_t es = dtype_size(dt);
   size_t off = 0;
-  for (int l = 0; l < 5; ++l) {
+  for (int l = 0; l < 5 && dt == DN_F32; ++l) {
     L.w_off[l] = off;
     const size_t n = l == 0 ? (size_t)96 * 3 * K1
                             : (size_t)L_M[l] * (L_C[l] / L_G[l]) * L_R[l] * L_R[l];
-    off = align256(off + n * es);
+    off = align256(off + n * sizeof(float));
   }
   for (int l = 0; l < 5; ++l) {
     L.b_off[l] = off;
     off = align256(off + (size_t)L_M[l] * 4);
   }
   for (int l = 0; l < 5; ++l) {
-    L.s_off[l] = 0;
     L.s_off[l] = off;
     const size_t n = l == 0 ? (size_t)(dt == DN_F32 ? 3 * K1 : C1_KSTEPS * 16) * 96
                             : (size_t)L_M[l] * (L_C[l] / L_G[l]) * L_R[l] * L_R[l];
-    off = align256(off + (dt == DN_F32 ? n * 3 * 2 : n * es));
+    off = align256(off + n * (dt == DN_F32 ? 3 * 2 : dtype_size(dt)));
   }
   if (dt == DN_F32) {
     L.special_off = off;
@@ -2254,45 +2243,28 @@ int launch_pack_weights(const float* const* d_w, const float* const* d_b, dn_dty
   uint32_t* special = (uint32_t*)(base + L.special_off);
   if (dt == DN_F32) clear_words_kernel<<<1, 64, 0, s>>>(special, 5);
   for (int l = 0; l < 5; ++l) {
-    void* dst = base + L.w_off[l];
+    void* wd = base + L.w_off[l];
+    void* sd = base + L.s_off[l];
     if (l == 0) {
-      const int n = 96 * 3 * K1;
-      if (dt == DN_F32) pack_conv1_kernel<float><<<(n + 255) / 256, 256, 0, s>>>(d_w[0], (float*)dst);
-      if (dt == DN_F16)
-        pack_conv1_kernel<_Float16><<<(n + 255) / 256, 256, 0, s>>>(d_w[0], (_Float16*)dst);
-      if (dt == DN_BF16) pack_conv1_kernel<__bf16><<<(n + 255) / 256, 256, 0, s>>>(d_w[0], (__bf16*)dst);
+      const int n = 96 * 3 * K1, nr = C1_KSTEPS * 96 * 16;
+      if (dt == DN_F32) {
+        pack_conv1_kernel<<<(n + 255) / 256, 256, 0, s>>>(d_w[0], (float*)wd);
+        pack_split1_kernel<<<(n + 255) / 256, 256, 0, s>>>(d_w[0], (__bf16*)sd, special);
+      }
+      if (dt == DN_F16) pack_conv1_resident_kernel<_Float16><<<(nr + 255) / 256, 256, 0, s>>>(d_w[0], (_Float16*)sd);
+      if (dt == DN_BF16) pack_conv1_resident_kernel<__bf16><<<(nr + 255) / 256, 256, 0, s>>>(d_w[0], (__bf16*)sd);
     } else {
-      const int Cg = L_C[l] / L_G[l], RR = L_R[l] * L_R[l];
-      const int64_t n = (int64_t)L_M[l] * Cg * RR;
+      const int Cg = L_C[l] / L_G[l], Mg = L_M[l] / L_G[l], R = L_R[l];
+      const int64_t n = (int64_t)L_M[l] * Cg * R * R;
       const unsigned nb = (unsigned)((n + 255) / 256);
-      if (dt == DN_F32) pack_conv_kernel<float><<<nb, 256, 0, s>>>(d_w[l], (float*)dst, L_M[l], Cg, RR);
-      if (dt == DN_F16)
-        pack_conv_kernel<_Float16><<<nb, 256, 0, s>>>(d_w[l], (_Float16*)dst, L_M[l], Cg, RR);
-      if (dt == DN_BF16)
-        pack_conv_kernel<__bf16><<<nb, 256, 0, s>>>(d_w[l], (__bf16*)dst, L_M[l], Cg, RR);
+      if (dt == DN_F32) {
+        pack_conv_kernel<<<nb, 256, 0, s>>>(d_w[l], (float*)wd, L_M[l], Cg, R * R);
+        pack_split_kernel<<<nb, 256, 0, s>>>(d_w[l], (__bf16*)sd, special + l, Mg, Cg, R * R, n);
+      }
+      if (dt == DN_F16) pack_stage_kernel<_Float16><<<nb, 256, 0, s>>>(d_w[l], (_Float16*)sd, Mg, Cg, R, L_BM[l], n);
+      if (dt == DN_BF16) pack_stage_kernel<__bf16><<<nb, 256, 0, s>>>(d_w[l], (__bf16*)sd, Mg, Cg, R, L_BM[l], n);
     }
     copy_f32_kernel<<<(L_M[l] + 255) / 256, 256, 0, s>>>(d_b[l], (float*)(base + L.b_off[l]), L_M[l]);
-    if (L.s_off[l] && l == 0) {
-      const int n = C1_KSTEPS * 96 * 16;
-      void* sd = base + L.s_off[0];
-      if (dt == DN_F32)
-        pack_split1_kernel<<<(3 * K1 * 96 + 255) / 256, 256, 0, s>>>(d_w[0], (__bf16*)sd, special);
-      if (dt == DN_F16)
-        pack_conv1_resident_kernel<_Float16><<<(n + 255) / 256, 256, 0, s>>>(d_w[0], (_Float16*)sd);
-      if (dt == DN_BF16)
-        pack_conv1_resident_kernel<__bf16><<<(n + 255) / 256, 256, 0, s>>>(d_w[0], (__bf16*)sd);
-    } else if (L.s_off[l]) {
-      const int Cg = L_C[l] / L_G[l], Mg = L_M[l] / L_G[l];
-      const int64_t n = (int64_t)L_M[l] * Cg * L_R[l] * L_R[l];
-      const unsigned nb = (unsigned)((n + 255) / 256);
-      void* sd = base + L.s_off[l];
-      if (dt == DN_F32)
-        pack_split_kernel<<<nb, 256, 0, s>>>(d_w[l], (__bf16*)sd, special + l, Mg, Cg, L_R[l] * L_R[l], n);
-      if (dt == DN_F16)
-        pack_stage_kernel<_Float16><<<nb, 256, 0, s>>>(d_w[l], (_Float16*)sd, Mg, Cg, L_R[l], L_BM[l], n);
-      if (dt == DN_BF16)
-        pack_stage_kernel<__bf16><<<nb, 256, 0, s>>>(d_w[l], (__bf16*)sd, Mg, Cg, L_R[l], L_BM[l], n);
-    }
   }
   return (int)hipGetLastError();
 }
