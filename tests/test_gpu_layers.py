@@ -321,8 +321,7 @@ def test_f32_split_conv_values_that_do_not_split(D, layer, value, where):
 
 @pytest.mark.parametrize("dt", ["f16", "bf16"])
 # the smallest plane; a last row whose 16-byte slot would pass the plane's end; several tiles per row
-# and column; more wave tiles than workers (256 CUs x 8) so that a worker takes several; rows on 16 bytes
-# from an unaligned pointer.
+# and column; many planes; rows on 16 bytes from an unaligned pointer.
 @pytest.mark.parametrize("n,H,W,shift", [(3, 11, 11, 0), (1, 13, 17, 1), (2, 67, 139, 0), (40, 131, 227, 1),
                                          (2, 40, 64, 3)])
 def test_conv1_rows_at_any_alignment(D, dt, n, H, W, shift):
@@ -360,30 +359,154 @@ def test_lrn_pool_f32_registers(D, C, shape):
     assert bool(((out - ref).abs() <= 2e-6 * ref.abs() + 1e-30).all())
 
 
+def conv_route(layer, runs, cus):
+    """The kernel that a 16-bit launch of conv2-5 over runs [(n, H, W)] takes on a device of cus CUs: "tiles", or
+    pixel sequences of so many pixels and channels per workgroup (the library's dispatch rule, restated)."""
+    M, C, R, _, _, _ = LAYERS[layer - 1]
+    pad = (R - 1) // 2
+
+    def mfma_tiles(n, H, W, th, tw):
+        t = 0
+        for y in range(0, H, th):
+            for x in range(0, W, tw):
+                rows, cols = (min(th, H - y) + 1) // 2 * (tw // 16), (min(tw, W - x) + 1) // 2
+                t += min(rows, cols) if th == 16 else rows
+        return n * t
+
+    def fits(pt, positions):
+        for n, H, W in runs:
+            rows, planes = (pt - 2) // W + 1, (pt - 2) // (H * W) + 1 if n > 1 else 0
+            if pt + rows * pad + planes * pad * (W + pad) + 2 * pad * (W + pad + 1) + 1 > positions:
+                return False
+        return True
+
+    def blocks(pt, bm):
+        return sum(-(-n * H * W // pt) for n, H, W in runs) * (M // bm)
+
+    def tiles(bm):
+        return sum(n * -(-H // 16) * -(-W // 16) for n, H, W in runs) * (M // bm)
+
+    tw = 32 if layer == 2 else 16
+    fills = 10 * sum(mfma_tiles(*r, 16, tw) for r in runs) >= 11 * sum(-(-n * H * W // 32) for n, H, W in runs)
+    if layer == 2:
+        return "512x64" if fills and fits(512, 832) and blocks(512, 64) >= 4 * cus else "tiles"
+    if blocks(128, 64) <= 2 * cus and fits(128, 320):
+        return "128x64"
+    if fills and fits(256, 384):
+        bm, per_cu = (192, 2) if layer == 4 else (128, 3)
+        if tiles(bm) >= 2 * cus * per_cu:
+            return f"256x{bm}"
+        if 2 * blocks(256, 64) >= 3 * cus:
+            return "256x64"
+    return "tiles"
+
+
+def cu_count():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
 # Launches of many small maps: pixels as sequences across rows and planes, in each of its configurations
 # (layer 2 and layers 3 to 5 large; 3 to 5 medium; at most two workgroups per CU), with maps of one row or
-# column, planes shorter than a workgroup's pixels and a partly filled last workgroup.
-@pytest.mark.parametrize("layer,n,H,W", [(2, 200, 27, 27), (2, 900, 11, 19), (3, 700, 13, 13), (4, 700, 13, 13),
-                                         (5, 1100, 13, 13), (3, 150, 13, 13), (4, 64, 17, 23), (5, 200, 13, 14),
-                                         (3, 40, 13, 13), (5, 7, 1, 40), (4, 5, 33, 1), (3, 2, 60, 60)])
-def test_conv_pixel_sequences(D, layer, n, H, W):
+# column, planes shorter than a workgroup's pixels and a partly filled last workgroup; rows too long for them.
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("layer,n,H,W,route", [
+    (2, 200, 27, 27, "512x64"), (2, 900, 11, 19, "512x64"), (3, 700, 13, 13, "256x128"), (4, 700, 13, 13, "256x192"),
+    (5, 1100, 13, 13, "256x128"), (3, 150, 13, 13, "256x64"), (4, 64, 17, 23, "256x64"), (5, 200, 13, 14, "256x64"),
+    (3, 40, 13, 13, "128x64"), (5, 7, 1, 40, "tiles"), (5, 20, 1, 13, "128x64"),
+    (4, 5, 33, 1, "128x64"), (3, 2, 60, 60, "128x64")])
+def test_conv_pixel_sequences(D, dt, layer, n, H, W, route):
     """Sampled planes equal, bit for bit, the same plane computed in a launch of its own (whose workgroups
-    hold other pixels of it), and the first and last equal fp64 to bf16's rounding."""
+    hold other pixels of it), and the first and last equal fp64 to the type's rounding."""
+    assert conv_route(layer, [(n, H, W)], cu_count()) == route or cu_count() != 256
     g = torch.Generator().manual_seed(layer * 1000 + n)
     C = LAYERS[layer - 1][1]
-    x = (torch.randn((n, H, W, C), generator=g) * 20).clamp(min=0).to(torch.bfloat16).cuda()
-    pk = packed(D, "bf16")
-    out = D.densenet_conv_layer(layer, x, n, H, W, DTS["bf16"], pk)
+    x = (torch.randn((n, H, W, C), generator=g) * 20).clamp(min=0).to(TORCH_DT[dt]).cuda()
+    pk = packed(D, dt)
+    out = D.densenet_conv_layer(layer, x, n, H, W, DTS[dt], pk)
     for i in sorted({0, 1, n // 3, n // 2, n - 2, n - 1}):
-        one = D.densenet_conv_layer(layer, x[i:i + 1].contiguous(), 1, H, W, DTS["bf16"], pk)
+        one = D.densenet_conv_layer(layer, x[i:i + 1].contiguous(), 1, H, W, DTS[dt], pk)
         assert torch.equal(one[0].view(torch.int16), out[i].view(torch.int16)), f"plane {i}"
     w, b = (torch.from_numpy(v) for v in W7[layer - 1])
     _, _, R, s, p, G = LAYERS[layer - 1]
     for i in (0, n - 1):
-        ref = torch.nn.functional.conv2d(x[i:i + 1].double().cpu().permute(0, 3, 1, 2), w.bfloat16().double(),
+        ref = torch.nn.functional.conv2d(x[i:i + 1].double().cpu().permute(0, 3, 1, 2), w.to(TORCH_DT[dt]).double(),
                                          b.double(), s, p, 1, G).clamp(min=0).permute(0, 2, 3, 1)[0]
-        # half an ulp of bf16 (2^-9 relative to the value's binade: 2^-8 of the value) and fp32 sums
-        assert bool(((out[i].double().cpu() - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-3).all())
+        # half an ulp (2^-9 or 2^-12 relative to the value's binade: twice that of the value) and fp32 sums
+        half_ulp = {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dt]
+        assert bool(((out[i].double().cpu() - ref).abs() <= half_ulp * ref.abs() + 1e-3).all())
+
+
+# layers 2 to 5: the large configurations over several runs, and the medium ones
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("n,routes", [((450, 400), ("512x64", "256x128", "256x192", "256x128")),
+                                      ((130, 1, 110), ("512x64", "256x64", "256x64", "256x64"))])
+def test_conv_pixel_sequences_several_runs(D, dt, n, routes):
+    """The whole stack over runs of planes of different sizes: sampled planes equal, bit for bit, the same
+    plane alone in a call."""
+    sizes = [(227, 227), (211, 243), (243, 195)][:len(n)]
+    hw = [D.layer_sizes(h, w) for h, w in sizes]
+    for layer, route in zip((2, 3, 4, 5), routes):
+        runs = [(k, *s[{2: 1, 3: 3}.get(layer, 4)]) for k, s in zip(n, hw)]
+        assert conv_route(layer, runs, cu_count()) == route or cu_count() != 256
+    descs, off = [], 0
+    for k, (h, w) in zip(n, sizes):
+        for _ in range(k):
+            d = D.dn_plane_desc()
+            d.h, d.w, d.pitch, d.offset = h, w, -(-w // 8) * 8, off
+            off += 3 * h * d.pitch
+            descs.append(d)
+    planes = (torch.randn(off, generator=torch.Generator("cuda").manual_seed(3), device="cuda") * 50).to(TORCH_DT[dt])
+    maps = D.densenet_conv_features(planes, descs, DTS[dt], packed(D, dt), D.net_params()).conv5_maps()
+    for i in sorted({0, n[0] // 2, n[0] - 1, n[0], n[0] + 1, len(descs) - 2, len(descs) - 1}):
+        one = D.densenet_conv_features(planes, [descs[i]], DTS[dt], packed(D, dt), D.net_params()).conv5_maps()[0]
+        assert torch.isfinite(one.float()).all() and bool((one > 0).any())
+        assert torch.equal(one.view(torch.int16), maps[i].view(torch.int16)), f"plane {i}"
+
+
+# whole rounds of wave tiles over all workers and a remainder: below a tile per workgroup, and above
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("rounds,extra", [(2, 3), (1, 10), (3, 0)])
+def test_conv1_rows_at_any_alignment_several_tiles_per_worker(D, dt, rounds, extra):
+    """Workers (CUs x 8) that take `rounds` wave tiles of 4 x 16 output pixels each and some one more, from rows at
+    odd addresses: bit-identical to rows on 16 bytes."""
+    H, W, per = 131, 227, 32      # 31 x 55 outputs: 8 x 4 wave tiles
+    workers = 8 * cu_count()
+    n = -(-rounds * workers // per) + extra
+    assert rounds * workers <= n * per < (rounds + 1) * workers
+    g = torch.Generator("cuda").manual_seed(n)
+    x = (torch.randn((n, 3, H, W), generator=g, device="cuda") * 50).to(TORCH_DT[dt])
+    aligned = torch.zeros((n, 3, H, 232), dtype=x.dtype, device="cuda")
+    aligned[..., :W] = x
+    out = D.densenet_conv_layer(1, x, n, H, W, DTS[dt], packed(D, dt))
+    ref = D.densenet_conv_layer(1, aligned, n, H, 232, DTS[dt], packed(D, dt))[:, :, :(W - 11) // 4 + 1]
+    assert torch.isfinite(out.float()).all()
+    assert torch.equal(out.view(torch.int16), ref.contiguous().view(torch.int16))
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+def test_conv1_rows_at_any_alignment_several_runs(D, dt):
+    """Runs of two plane sizes with odd pitches (NaN between the rows) and more than two wave tiles per worker:
+    conv5 is bit-identical to that of the same planes on pitches of 8."""
+    sizes = ((131, 227, 32), (83, 163, 15))   # and wave tiles of a plane
+    n = [-(-cu_count() * 8 // per) + 1 for _, _, per in sizes]
+    maps = []
+    for odd in (True, False):
+        g = torch.Generator("cuda").manual_seed(9)
+        descs, parts, off = [], [], 0
+        for k, (h, w, _) in zip(n, sizes):
+            pitch = w + 2 if odd else -(-w // 8) * 8
+            rows = torch.full((k, 3, h, pitch), float("nan") if odd else 0.0, device="cuda")
+            rows[..., :w] = torch.randn((k, 3, h, w), generator=g, device="cuda") * 50
+            parts.append(rows.view(-1))
+            for _ in range(k):
+                d = D.dn_plane_desc()
+                d.h, d.w, d.pitch, d.offset = h, w, pitch, off
+                off += 3 * h * pitch
+                descs.append(d)
+        planes = torch.cat(parts).to(TORCH_DT[dt])
+        maps.append(D.densenet_conv_features(planes, descs, DTS[dt], packed(D, dt), D.net_params()).conv5)
+    assert torch.isfinite(maps[0].float()).all()
+    assert torch.equal(maps[0].view(torch.int16), maps[1].view(torch.int16))
 
 
 # Tile edges, partial tiles in both layouts, several chunks and groups, rows of odd length in conv1.
