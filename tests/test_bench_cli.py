@@ -20,6 +20,12 @@ def test_more_than_one_gpu_is_refused():
     assert r.stdout == ""
 
 
+def test_fp32_peak_counts_the_bf16_products():
+    """An fp32 value is three bf16 parts and a product six of theirs: the share of the bf16 peak that the matrix
+    cores reach is six times the fp32 work's share of it, at most 1."""
+    assert bench.PEAK_TFLOPS["f32"] * 6 == bench.PEAK_TFLOPS["bf16"] == bench.PEAK_TFLOPS["f16"]
+
+
 def test_source_digest_is_stable_and_short():
     a, b = bench.source_digest(), bench.source_digest()
     assert a == b and len(a) == 16
