@@ -1496,7 +1496,7 @@ __device__ inline void wait_vmem_upto() {
 // DIRECT = false, for rows at any alignment (pitches that are not multiples of 8, unaligned pointers,
 // planes beyond 2^31 bytes): the halo is loaded into registers, 16 bytes at 2-byte alignment, and
 // written to LDS where the direct loads are waited for, with the columns past the row's end zeroed.
-// 64 planes of 227 x 227 in fp16: 24.7 us (0.55 PFLOP/s), against 82 for a kernel of 16 x 16 tiles per
+// 64 planes of 227 x 227 in fp16: 22.3 us (0.60 PFLOP/s), against 82 for a kernel of 16 x 16 tiles per
 // workgroup that loaded such rows value by value.
 // ------------------------------------------------------------------------------------------------
 // PT: 32-pixel MFMA tiles per wave (2: wave tiles of 4 x 16 pixels, 8 waves per workgroup, two per

@@ -336,7 +336,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 // maximum of three input rows, the top one kept from the output row above.  The next input row's loads
 // are issued before the current row's LRN.  No LDS and no barriers, every thread busy: (5 / 4) x
 // (2 SR + 1) / (2 SR) of the LRN work.  Bound by memory: 16 maps of 59 x 79 x 256 take 22 us (4.3 TB/s of
-// compulsory bytes) against 73 us with a pixel's channels split over two threads and an LDS tile (110
+// compulsory bytes, 21-23 from box to box) against 73 us with a pixel's channels split over two threads and an LDS tile (110
 // of 256 threads busy, two workgroups per CU).
 template <int C, int SR, bool MULTI>
 __global__ __launch_bounds__(256) void lrn_pool_f32_kernel(const float* __restrict__ in, float* __restrict__ out,
@@ -795,8 +795,9 @@ int run(const void* d_in, const MapRun* runs, int n_runs, int32_t C, bool lrn, b
   } else {
     if (lrn && hn == 2 && (C == 96 || C == 256)) {
       // Three pooled rows per thread, or one where that leaves CUs without a workgroup: the
-      // maps of a two-scale 227 x 227 pyramid take 3.5 us each against 6.5 at three (whose chain of rows
-      // sets the time), 16 maps of 59 x 79 x 256 18.0 us at three, 18.5 at two and four, 23 at eight.
+      // maps of a two-scale 227 x 227 pyramid take 5.9 us after conv1 and 5.6 after conv2 against 9.5 and 8.5 at
+      // three (whose chain of rows sets the time), 16 maps of 59 x 79 x 256 21.0 us at three, 22.0 at two, 21.4 at
+      // four, 25.1 at eight.
       const int cols = 2 * (256 / (C / 4));
       int64_t blocks = tiles(3, cols);
       const bool small = blocks > 0 && blocks < device_cus();

@@ -13,8 +13,8 @@
 // this path, so they need not displace the conv5 maps from the caches).  Max-pooled bins are values of the
 // maps, so their row is staged in the storage type: half the LDS (18.6 KB at 16 bits), eight workgroups per
 // CU instead of four, which is what hides a box's serial steps (choice, bin ranges, gather, write).  2000 boxes
-// of fp16 maps, pooled: 34 us with fp32 rows and one cell load in flight, 25 with stored values, 22 with
-// four loads in flight (3.4 TB/s of descriptors written).
+// of fp16 maps, pooled: 37 us with fp32 rows and one cell load in flight, 24 as it is
+// (3.1 TB/s of descriptors written).
 #include <type_traits>
 
 #include "common.h"
