@@ -207,7 +207,8 @@ int densenet_build_batch(const uint8_t* d_images, int32_t n_img, int32_t H, int3
 
 /* Repack conv1..conv5 weights for the kernels.  d_w[l]: device fp32 OIHW weights of layer l
  * (96x3x11x11, 256x48x5x5, 384x256x3x3, 384x192x3x3, 256x192x3x3); d_b[l]: device fp32 biases.
- * d_packed: output blob in `dtype` (biases stay fp32), or NULL for a size query. */
+ * d_packed: output blob in `dtype` (biases stay fp32), or NULL for a size query.  Its layout is that of the
+ * library's kernels and may differ from one build to the next: keep the weights, not the blob. */
 int densenet_pack_weights(const float* const* d_w, const float* const* d_b, dn_dtype dtype,
                           void* d_packed, size_t packed_bytes, size_t* bytes_needed, void* stream);
 
