@@ -26,10 +26,10 @@ namespace {
 // Packed weight layout
 //   conv1, fp32: [96][3][144], k = 16 s + 8 h + 4 j + e holds tap ky = 4 (s / 3) + 2 h + j,
 //          kx = 4 (s % 3) + e (zero where ky or kx is 11)
-//   conv2..5, fp32: [M][R*R][C/G] (tap-major, channels contiguous); these copies are read where values do not split
+//   conv2..5, fp32: [M][R*R][C/G] (tap-major, channels contiguous); both are read where values do not split
 //   conv1, 16-bit types: see pack_conv1_resident_kernel
-//   conv2..5, 16-bit types, stage-major for conv_s1_direct_kernel and conv_flat_kernel: per channel block (group g,
-//          block of BM output channels) and stage (chunk of 16 input channels, kernel row ky), one
+//   conv2..5, 16-bit types, stage-major for conv_s1_direct_kernel and conv_flat_kernel: per channel block
+//          (group g, block of BM output channels) and stage (chunk of 16 input channels, kernel row ky), one
 //          contiguous block of R * BM * 2 16-byte pieces, piece (kx BM + m) 2 + p holding input
 //          channels 8 (p ^ ((m >> 4) & 1)) .. + 7 of the chunk at tap (ky, kx) of channel m: exactly
 //          the order of the LDS weight-row buffer, so each direct load reads 1 KB of contiguous memory
@@ -802,17 +802,18 @@ __global__ __launch_bounds__(64 * (BM / (32 * TM)) * WN, OCC) void conv_flat_ker
 // Henry, Tang and Heinecke ("Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision
 // Computations", ARITH 2019).  A value is x = h + m + l, each the nearest bf16 of what is left: exact, with
 // |m| <= 2^-8 |x| and |l| <= 2^-17 |x|.  A product x w is taken as h h' + (h m' + m h') + (m m' + h l' + l h');
-// the dropped m l' + l m' + l l' are at most 2^-24 (1 + 2^-10) |x w| and of both signs, so one product may be off by
-// about the half ulp that rounding it to fp32 would cost (an fp32 MFMA rounds its sum only).  Six bf16 MFMAs replace eight fp32
-// ones of the same k, and run at 16 times their rate.  h h' and the five small terms are summed in
-// accumulators of their own, so the sum of the large terms is rounded once per 16 k (the fp32 MFMA
-// rounds it once per 2 k): over a layer's K the error against 64 bits falls two to three times.
-// Values that do not split (infinities, NaN, and finite values from 5.2e33) are seen
-// as they are staged (inputs) or packed (weights), and products that pass fp32's range in the sums (there the
-// products of the parts are infinities of both signs; as sums are 2^32 times too large, from 7.9e28); a workgroup that meets one computes its sums
-// from the fp32 data with fp32 MFMAs instead (after its split sums; at once where a weight is the cause).  An
-// infinite weight: conv3 on 8 maps of 37 x 49 524 us, conv2 on 8 of 59 x 79 282, conv1 on 8 planes of 480 x 640
-// 199, against 164, 128 and 88 us where all values split, and 51, 47 and 12 ms with one thread per pixel.
+// the dropped m l' + l m' + l l' are at most 2^-24 (1 + 2^-10) |x w| and of both signs, so one product may be
+// off by about the half ulp that rounding it to fp32 would cost (an fp32 MFMA rounds its sum only).  Six bf16
+// MFMAs replace eight fp32 ones of the same k, and run at 16 times their rate.  h h' and the five small terms
+// are summed in accumulators of their own, so the sum of the large terms is rounded once per 16 k (the fp32
+// MFMA rounds it once per 2 k): over a layer's K the error against 64 bits falls two to three times.
+// Values that do not split (infinities, NaN, and finite values from 5.2e33) are seen as they are staged
+// (inputs) or packed (weights), and products that pass fp32's range in the sums (there the products of the
+// parts are infinities of both signs; as sums are 2^32 times too large, from 7.9e28).  A workgroup that meets
+// one computes its sums from the fp32 data with fp32 MFMAs instead (after its split sums; at once where a
+// weight is the cause).  An infinite weight: conv3 on 8 maps of 37 x 49 524 us, conv2 on 8 of 59 x 79 282, conv1
+// on 8 planes of 480 x 640 199, against 164, 128 and 88 us where all values split, and 51, 47 and 12 ms with one
+// thread per pixel.
 //
 // Workgroup: 16 x 16 output pixels x 64 channels of one group, four waves of 64 channels x 64 pixels.
 // LDS holds one halo of 16 input channels as three bf16 planes, and two buffers of three taps' weights,
@@ -830,13 +831,14 @@ __device__ inline f32x16 mma_f32(float a, float b, f32x16 c) {
 
 // The larger of m and every |v|; NaN when any is NaN (two values per v_maximum3_f32).
 __device__ inline float max_or_nan(float m, const f32x16& v) {
+  auto larger = [](float p, float q) { return __builtin_elementwise_maximum(p, q); };
   float a = m, b = 0.f;
 #pragma unroll
   for (int e = 0; e < 16; e += 4) {
-    a = __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, __builtin_fabsf(v[e])), __builtin_fabsf(v[e + 1]));
-    b = __builtin_elementwise_maximum(__builtin_elementwise_maximum(b, __builtin_fabsf(v[e + 2])), __builtin_fabsf(v[e + 3]));
+    a = larger(larger(a, __builtin_fabsf(v[e])), __builtin_fabsf(v[e + 1]));
+    b = larger(larger(b, __builtin_fabsf(v[e + 2])), __builtin_fabsf(v[e + 3]));
   }
-  return __builtin_elementwise_maximum(a, b);
+  return larger(a, b);
 }
 
 template <int R>
@@ -927,7 +929,8 @@ __global__ __launch_bounds__(256, 2) void conv_f32_kernel(
     for (int i = 0; i < P::HALO_PER; ++i)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const uint32_t bits = __builtin_bit_cast(uint32_t, SPLIT_SCALE * __builtin_bit_cast(float, (uint32_t)hreg[i][q]));
+        const float v = SPLIT_SCALE * __builtin_bit_cast(float, (uint32_t)hreg[i][q]);
+        const uint32_t bits = __builtin_bit_cast(uint32_t, v);
         hreg[i][q] = bits;
         top = max(top, bits & 0x7fffffffu);
       }
@@ -1222,7 +1225,8 @@ __global__ __launch_bounds__(256, 2) void conv1_f32_kernel(const float* __restri
   constexpr uint32_t OOB = 0x80000000u;
 
   // Halo loads: four pixels of a row each, at byte offsets from the tile's first row (the rows of one
-  // channel, less than 2^31 bytes, or `wide` is set; 16-byte loads at 4-byte alignment).  Columns from W on are replaced by zeros.
+  // channel, less than 2^31 bytes, or `wide` is set; 16-byte loads at 4-byte alignment).  Columns from W on
+  // are replaced by zeros.
   const int rows = min(P::HR, H - iy0);
   uint32_t hoff[P::HALO_PER];
 #pragma unroll
@@ -1480,8 +1484,9 @@ __device__ inline void wait_vmem_upto() {
 
 // ------------------------------------------------------------------------------------------------
 // conv1 for 16-bit storage with direct global->LDS loads (DIRECT: rows that start on 16 bytes), weights
-// resident, one independent pipeline per wave.  A workgroup of 8 waves (one per CU, two waves per SIMD) loads all weights (75 KB) into LDS once, as 25 k-steps of 16 (the 363
-// taps of an output channel as 99 units of 4 taps: see pack_conv1_resident_kernel) x 96 channels x
+// resident, one independent pipeline per wave.  A workgroup of 8 waves (one per CU, two waves per SIMD) loads
+// all weights (75 KB) into LDS once, as 25 k-steps of 16 (the 363 taps of an output channel as 99 units of
+// 4 taps: see pack_conv1_resident_kernel) x 96 channels x
 // two 16-byte slots, the slots swapped for channels 16..31 of every 32-channel group, so that the 32
 // lanes of a half-wave reading one k-step's 16 bytes of 32 channels hit distinct slots modulo 512
 // bytes.  After that every wave is its own worker with no workgroup barrier: it walks wave tiles of 4
@@ -1744,7 +1749,8 @@ __global__ __launch_bounds__(64 * Conv1R<PT>::NWV, 1) void conv1_resident_kernel
       static_for<J0, J1>(body);
     };
     // stage 0: channel 0 in X; channel 1 loads into Y
-    ksteps(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{}, hy, hx, [&] { load_halo((j + 1) & 1, 1); });
+    ksteps(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{}, hy, hx,
+           [&] { load_halo((j + 1) & 1, 1); });
     land((j + 1) & 1);
     // stage 1: channel 1 in Y (k-step 8 also reads channel 0 in X); channel 2 loads into X
     ksteps(std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{}, hx, hy, [&] { load_halo(j & 1, 2); });
@@ -2096,7 +2102,7 @@ int conv_dispatch(int layer, const void* d_in, const MapRun* runs, int n_runs, c
       // a tile's halo rows are addressed with 32-bit byte offsets (rows up to 7.4 million values apart)
       int wide = 0;
       for (int i = 0; i < n_runs; ++i)
-        if ((int64_t)Split1::HR * std::max(runs[i].pitch, runs[i].W) * (int64_t)sizeof(float) >= 0x7fffffffLL) wide = 1;
+        if ((int64_t)Split1::HR * std::max(runs[i].pitch, runs[i].W) * 4 >= 0x7fffffffLL) wide = 1;
       if (n_runs == 1)
         conv1_f32_kernel<false><<<(unsigned)(blocks * ks), 256, 0, s>>>(in, out, wsplit, wp, special, bias, kr, ks,
                                                                          (int)blocks, part, span, wide);
@@ -2160,8 +2166,9 @@ int conv_dispatch(int layer, const void* d_in, const MapRun* runs, int n_runs, c
     }
     // The 16-bit kernels address one plane with 32-bit byte offsets.  Refused first: the counts below are
     // then of maps below 2^31 bytes.
+    const int64_t most = 0x7ffffffeLL / (L_C[li] * (int64_t)sizeof(T));  // pixels
     for (int i = 0; i < n_runs; ++i)
-      if ((int64_t)runs[i].H * runs[i].W > 0x7ffffffeLL / (L_C[li] * (int64_t)sizeof(T))) return (int)hipErrorInvalidValue;
+      if ((int64_t)runs[i].H * runs[i].W > most) return (int)hipErrorInvalidValue;
 #define DN_RUN_ARGS in, out, ws, bias, runs, n_runs, L_C[li], L_G[li], L_M[li], s
 #define DN_SMALL_CFG(l) 3, 64, 2, DN_SMALL_OCC, 1616, L_BM[l], DN_SMALL_TN
 #define DN_FLAT_ARGS runs, n_runs, L_C[li], L_M[li]

@@ -336,8 +336,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 // maximum of three input rows, the top one kept from the output row above.  The next input row's loads
 // are issued before the current row's LRN.  No LDS and no barriers, every thread busy: (5 / 4) x
 // (2 SR + 1) / (2 SR) of the LRN work.  Bound by memory: 16 maps of 59 x 79 x 256 take 22 us (4.3 TB/s of
-// compulsory bytes, 21-23 from box to box) against 73 us with a pixel's channels split over two threads and an LDS tile (110
-// of 256 threads busy, two workgroups per CU).
+// compulsory bytes, 21-23 from box to box) against 73 us with a pixel's channels split over two threads and
+// an LDS tile (110 of 256 threads busy, two workgroups per CU).
 template <int C, int SR, bool MULTI>
 __global__ __launch_bounds__(256) void lrn_pool_f32_kernel(const float* __restrict__ in, float* __restrict__ out,
                                                            KRuns runs, float alpha_n, float beta, float k) {

@@ -269,8 +269,8 @@ def f32_layer(D, layer, x, weights):
                                          (2, (1, 1, 1)), (2, (2, 17, 33)), (3, (1, 2, 2)), (3, (2, 16, 16)),
                                          (3, (1, 33, 5)), (4, (2, 5, 35)), (5, (1, 18, 40))])
 def test_f32_split_conv(D, layer, shape):
-    """fp32 layers on bf16 matrix cores: the six products kept of x w leave out at most d |x w|, d = 2^-24 (1 + 2^-10) (parts
-    |m| <= 2^-8 |x| and |l| <= 2^-17 |x|: m l' + l m' + l l'), and the sum of K terms is rounded at most
+    """fp32 layers on bf16 matrix cores: the six products kept of x w leave out at most d |x w|,
+    d = 2^-24 (1 + 2^-10) (parts |m| <= 2^-8 |x| and |l| <= 2^-17 |x|: m l' + l m' + l l'), and the sum of K terms is rounded at most
     6 K / 16 + 2 times, each by half an ulp (2^-24) of a partial sum no larger than S = sum |x w| + |b|:
     |error| <= (d + (6 K / 16 + 2) 2^-24) S."""
     M, C, R, _, _, G = LAYERS[layer - 1]
